@@ -195,7 +195,8 @@ def prepare(case, seed):
     s["sector"] = ftlm.Sector(case["sites"], case["n_up"], mode, two_s=case.get("two_s", 1))
     if case["do"] == "hv":
         s["x"] = start_block(case, seed)
-        rows = share_rows(case)[1]
+        s["rows"] = share_rows(case)
+        rows = s["rows"][1]
         s["y"] = torch.empty((rows,) + tuple(s["x"].shape[1:]), dtype=s["x"].dtype, device=DEV)
     else:
         n = ftlm.lanczos_workspace_bytes(s["sector"], case["cols"], DTYPE[case["dtype"]])
@@ -220,11 +221,10 @@ def share_rows(case):
 def run(state):
     c = state["case"]
     if c["do"] == "hv":
-        row0, rows = share_rows(c)
-        if c.get("share", 1) == 1:
-            ftlm.hv(state["sector"], state["graph"], state["x"], state["y"])
+        if "share" in c:
+            ftlm.hv_rows(state["sector"], state["graph"], state["x"], state["y"], *state["rows"])
         else:
-            ftlm.hv_rows(state["sector"], state["graph"], state["x"], state["y"], row0, rows)
+            ftlm.hv(state["sector"], state["graph"], state["x"], state["y"])
         return {"y": state["y"]}
     if c["do"] == "lanczos":
         a, b, k = ftlm.lanczos(state["sector"], state["graph"], state["seed"], 0, c["cols"], c["steps"], DIST[c["dist"]],

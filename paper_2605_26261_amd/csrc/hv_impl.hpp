@@ -327,22 +327,22 @@ __device__ __forceinline__ void store_partials(const SecWork& sw, const LanczosL
     if (threadIdx.x < VB) {
         double t = 0.0;
         for (int w = 0; w < kWaves; ++w) t += wsum[w * VB + threadIdx.x];
-        sw.partials[size_t(slot) * a.ld + a.col0 + threadIdx.x] = t;
+        publish(sw.partials + size_t(slot) * a.ld + a.col0 + threadIdx.x, t);
     }
 }
 
-// alpha_k of the launch's columns of one sector from its n partial slots.
+// alpha_k of the launch's columns of one sector from its n partial slots, one
+// thread per column.
 template <int VB>
 __device__ __forceinline__ void finish_alpha(const SecWork& sw, const LanczosLaunch& a, uint32_t n, double* red) {
-    double tot[VB];
+    __shared__ double tot[grid_sum_slots<VB>()];
     grid_sum_cols<VB>(sw.partials, int(n), int(a.ld), int(a.col0), VB, red, tot);
-    if (threadIdx.x == 0) {
-        for (int c = 0; c < VB; ++c) {
-            Chain* ch = &sw.chains[a.col0 + c];
-            ch->alpha = ch->s_cur * tot[c];
-            ch->up_d = ch->alpha * ch->s_cur;
-            ch->up_f = float(ch->up_d);
-        }
+    if (threadIdx.x < VB) {
+        Chain* ch = &sw.chains[a.col0 + threadIdx.x];
+        const double alpha = ch->s_cur * tot[threadIdx.x], up = alpha * ch->s_cur;
+        ch->alpha = alpha;
+        ch->up_d = up;
+        ch->up_f = float(up);
     }
 }
 
@@ -354,8 +354,7 @@ __device__ __forceinline__ void finish_alpha(const SecWork& sw, const LanczosLau
 // The grid is persistent, sized to the resident workgroups: each workgroup
 // takes (sector, item) pairs from its XCD's counter (queue_item) and runs
 // them one after the other, and each item stores its partials in its own
-// slot with plain stores. The last workgroup to leave (queue_exit, the one
-// device-scope fence of each workgroup) sums every sector's slots. Which
+// slot. The last workgroup to leave (queue_exit) sums every sector's slots. Which
 // workgroup ran an item changes nothing: the tiles of an item, its partial
 // slot and the summation order depend on the sector's dimension only.
 template <typename L, int MODE, typename T, int VB>
@@ -442,6 +441,7 @@ hipError_t launch_lanczos_one(const LanczosLaunch& a, size_t lds, hipStream_t st
     auto kern = hv_lanczos_kernel<L, MODE, T, VB>;
     const size_t floor = lanczos_lds_floor<MODE, T, VB>(a.max_dim);
     if (lds < floor) lds = floor;
+    if (lds < kGridSumLds) lds = kGridSumLds;  // the final sums reuse the block's LDS
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));

@@ -463,12 +463,13 @@ hipError_t launch_hv_lanczos_spin(const LanczosLaunch& a, size_t lds, hipStream_
         return with_spin_vb(a.vb, [&](auto vb) {
             auto kern = hv_spin_lanczos_kernel<MODE, T, decltype(vb)::value>;
             if (!a.queue || a.items <= 0) return hipErrorInvalidValue;  // the queue counters are required
-            hipError_t e = allow_lds(kern, lds);
+            const size_t bytes = lds < kGridSumLds ? kGridSumLds : lds;  // the final sums reuse the block's LDS
+            hipError_t e = allow_lds(kern, bytes);
             if (e != hipSuccess) return e;
             int grid = 0;
-            e = persistent_grid(reinterpret_cast<const void*>(kern), lds, a.items, &grid);
+            e = persistent_grid(reinterpret_cast<const void*>(kern), bytes, a.items, &grid);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kBlock), lds, st, a);
+            hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kBlock), bytes, st, a);
             return hipGetLastError();
         });
     };

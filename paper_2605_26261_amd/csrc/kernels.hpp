@@ -256,30 +256,6 @@ __device__ __forceinline__ int queue_item(const SecWork* secs, int nsec, uint32_
     return -1;
 }
 
-// Called by every block of a persistent launch after its last item. Every
-// thread's writes (outputs and reduction partials) are released, then the
-// block counts itself out; returns true in the last block to get here, with
-// every other block's writes visible to it, after it has zeroed the counters
-// for the next launch (every block has stopped taking items). These are the
-// only device-scope fences of the launch: on gfx950 such a fence writes back
-// and invalidates the XCD's L2, which a fence per work item would do
-// thousands of times while other workgroups still gather from it.
-__device__ __forceinline__ bool queue_exit(uint32_t* q, uint32_t grid, int* flag_lds) {
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t done = atomicAdd(q + 8, 1u);
-        const bool last = done == grid - 1u;
-        if (last)
-            for (int i = 0; i < kQueueWords; ++i) atomicExch(q + i, 0u);
-        *flag_lds = last ? 1 : 0;
-    }
-    __syncthreads();
-    const bool last = *flag_lds != 0;
-    if (last) __threadfence();
-    return last;
-}
-
 // The sector owning block `b` of a multi-sector launch, by a wave-uniform
 // scan of the block ranges; *local receives the block's index inside the
 // sector, or the function returns -1 for a padding block.

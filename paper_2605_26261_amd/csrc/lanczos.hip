@@ -78,7 +78,7 @@ __device__ __forceinline__ double start_entry(int dist, uint64_t key, uint64_t i
 // each chain's initial scale s_1 = 1 / |u_1|.
 template <typename T, int CB>
 __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
-    __shared__ double red[kBlock];
+    __shared__ double red[grid_sum_lds<CB>() / sizeof(double)];
     __shared__ int flag;
     uint32_t local = 0;
     const int s = sector_of_block(a.secs, a.nsec, blockIdx.x, &local);
@@ -105,17 +105,15 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
             }
         }
     });
-    block_sum<CB>(part, red);
-    if (threadIdx.x < nc) sw.partials[size_t(local) * a.ld + a.col0 + threadIdx.x] = red[kWaves * CB + threadIdx.x];
+    block_sum<CB>(part, red, sw.partials + size_t(local) * a.ld + a.col0, nc);
     if (last_block(sw.ticket, sw.G, &flag)) {
-        double tot[CB];
+        __shared__ double tot[grid_sum_slots<CB>()];
         grid_sum_cols<CB>(sw.partials, int(sw.G), int(a.ld), int(a.col0), nc, red, tot);
-        for (int c = 0; c < nc; ++c) {
-            const int col = int(a.col0) + c;
-            if (threadIdx.x == 0) {
-                Chain* ch = &sw.chains[col];
-                const double nrm = sqrt(tot[c]);
-                sw.state[1] += nrm > 0.0 ? 1 : 0;
+        if (threadIdx.x < 64) {  // one lane per column
+            const bool mine = int(threadIdx.x) < nc;
+            const double nrm = mine ? sqrt(tot[threadIdx.x]) : 0.0;
+            if (mine) {
+                Chain* ch = &sw.chains[a.col0 + threadIdx.x];
                 ch->norm = nrm;
                 ch->s_cur = nrm > 0.0 ? 1.0 / nrm : 0.0;
                 ch->s_prev = 0.0;
@@ -126,8 +124,12 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
                 ch->steps = 0;
                 chain_set_hv(ch);
             }
+            const int started = __popcll(__ballot(nrm > 0.0));
+            if (threadIdx.x == 0) {
+                sw.state[1] += started;
+                *sw.ticket = 0u;
+            }
         }
-        if (threadIdx.x == 0) *sw.ticket = 0u;
     }
 }
 
@@ -164,12 +166,15 @@ __host__ __device__ constexpr int update_stage_rows() {
 
 template <typename T, int VB>
 __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
-    __shared__ double red[kBlock];
     __shared__ int flag;
     constexpr bool kStage = update_staged<T, VB>();
     constexpr int kStageRows = update_stage_rows<T, VB>();
     __shared__ __align__(16) T stage_u[kStage ? kStageRows * VB : 1];
     __shared__ __align__(16) T stage_w[kStage ? kStageRows * VB : 1];
+    // the reductions come after the rows and reuse their LDS
+    constexpr bool kOwnRed = sizeof(stage_w) < grid_sum_lds<VB>();
+    __shared__ double own_red[kOwnRed ? grid_sum_lds<VB>() / sizeof(double) : 1];
+    double* red = kOwnRed ? own_red : reinterpret_cast<double*>(stage_w);
     uint32_t local = 0;
     const int s = sector_of_block(a.secs, a.nsec, blockIdx.x, &local);
     if (s < 0) return;
@@ -283,17 +288,18 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
         }
         store_row<T, VB>(wrow, ww);
     });
-    block_sum<VB>(part, red);
-    if (threadIdx.x < VB) sw.partials[size_t(local) * a.ld + a.col0 + threadIdx.x] = red[kWaves * VB + threadIdx.x];
+    __syncthreads();
+    block_sum<VB>(part, red, sw.partials + size_t(local) * a.ld + a.col0, VB);
     if (last_block(sw.ticket, sw.G, &flag)) {
-        double tot[VB];
+        __shared__ double tot[grid_sum_slots<VB>()];
         grid_sum_cols<VB>(sw.partials, int(sw.G), int(a.ld), int(a.col0), VB, red, tot);
-        for (int c = 0; c < VB; ++c) {
-            const int col = int(a.col0) + c;
-            if (threadIdx.x == 0) {
+        if (threadIdx.x < 64) {  // one lane per column
+            bool stopped = false;
+            if (threadIdx.x < VB) {
+                const int col = int(a.col0 + threadIdx.x);
                 Chain* ch = &sw.chains[col];
                 if (ch->active) {
-                    const double bk = sqrt(tot[c]);
+                    const double bk = sqrt(tot[threadIdx.x]);
                     const double ak = ch->alpha;
                     sw.alpha[size_t(col) * kMaxSteps + (step - 1)] = ak;
                     sw.beta[size_t(col) * kMaxSteps + (step - 1)] = bk;
@@ -305,8 +311,8 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
                     // is false for NaN, so without this the chain would run on
                     const bool fault = !(isfinite(ak) && isfinite(bk));
                     if (fault) ch->fault = 1;
-                    if (fault || step >= sw.m_eff || bk <= a.eps * amax) {
-                        sw.state[1] -= 1;
+                    stopped = fault || step >= sw.m_eff || bk <= a.eps * amax;
+                    if (stopped) {
                         ch->active = 0;
                         ch->s_cur = 0.0;
                         ch->s_prev = 0.0;
@@ -319,10 +325,12 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
                     chain_set_hv(ch);
                 }
             }
-        }
-        if (threadIdx.x == 0) {
-            if (a.last_chunk) sw.state[0] = step + 1;
-            *sw.ticket = 0u;
+            const int n = __popcll(__ballot(stopped));
+            if (threadIdx.x == 0) {
+                if (n) sw.state[1] -= n;
+                if (a.last_chunk) sw.state[0] = step + 1;
+                *sw.ticket = 0u;
+            }
         }
     }
 }

@@ -186,8 +186,8 @@ int ftlm_clt_export(const ftlm_sector* s, uint32_t* mask_host, uint32_t* prefix_
  * idx_dev[(t - t0) * n_bonds + b] = the sector index
  * of the partner label n_t XOR (2^i + 2^j) when sites i, j of bond b are
  * antiparallel in n_t, else FTLM_NONE (Eq. 12 at s = 1/2; Eqs. 13-14 give the
- * coefficient J_b / 2). The indices come from the same code the H.x kernels
- * use. idx_dev is device uint64[count * n_bonds]. For a general-spin sector
+ * coefficient J_b / 2). The indices come from the sector's own index map,
+ * through the row visitor of the row-by-row H.x kernel. idx_dev is device uint64[count * n_bonds]. For a general-spin sector
  * each bond b = (i, j), i < j, has two entries: idx_dev[(t - t0) * 2 n_bonds
  * + 2 b] is the index of the source state with a_i + 1, a_j - 1 and entry
  * 2 b + 1 the one with a_i - 1, a_j + 1 (the two ladder terms of Eq. 12), or
@@ -202,7 +202,10 @@ int ftlm_neighbors(const ftlm_sector* s, const ftlm_graph* g, uint64_t t0, uint6
  * state n_t as
  *   y[t] = sum_b J_b s^z_i s^z_j x[t] + sum_{b antiparallel} (J_b / 2) x[idx(n_t ^ mask_b)]
  * with s^z_i s^z_j = +-1/4, no atomics. dtype FTLM_F32 accumulates each row in
- * FP32, FTLM_F64 in FP64. x and y must not overlap. 1 <= nvec <= 64. */
+ * FP32, FTLM_F64 in FP64. x and y must not overlap. 1 <= nvec <= 64. Every
+ * index map gives the same bits: a row's terms are added in one order, and
+ * the kernel is chosen by size, filling and row width, so a sector with a
+ * stored map may be ranked where that is faster. */
 int ftlm_hv(const ftlm_sector* s, const ftlm_graph* g, const void* x_dev, void* y_dev, int nvec,
             int dtype, void* stream);
 

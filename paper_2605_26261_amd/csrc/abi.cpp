@@ -349,7 +349,6 @@ int ftlm_hv_rows(const ftlm_sector* s, const ftlm_graph* g, const void* x_dev, v
     h.row0 = uint32_t(row0);
     h.nrows = uint32_t(nrows);
     h.dtype = dtype;
-    h.grid = int(rows_grid(uint32_t(nrows)));
     for (auto [col, vb] : column_chunks(nvec, uint64_t(nvec), dtype, {x_dev, y_dev}, max_launch_width(s->two_s))) {
         h.col0 = uint32_t(col);
         h.vb = vb;

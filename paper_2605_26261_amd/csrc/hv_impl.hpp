@@ -5,61 +5,11 @@
 
 #include <type_traits>
 
+#include "rowio.hpp"
 #include "rowloop.hpp"
+#include "runs.hpp"
 
 namespace ftlm {
-
-// Loads/stores VB consecutive elements with the widest naturally aligned
-// vector access (the host only picks a vector width whose alignment holds),
-// as global-memory accesses.
-template <typename T, int N>
-using VecT = T __attribute__((ext_vector_type(N)));
-
-template <typename T, int VB>
-__device__ __forceinline__ void load_row(const T* __restrict__ p, T (&v)[VB]) {
-    if constexpr (sizeof(T) == 4 && VB % 4 == 0) {
-#pragma unroll
-        for (int i = 0; i < VB; i += 4) {
-            const VecT<T, 4> q = *(const FTLM_GLOBAL VecT<T, 4>*)(p + i);
-            v[i] = q.x; v[i + 1] = q.y; v[i + 2] = q.z; v[i + 3] = q.w;
-        }
-    } else if constexpr (VB % 2 == 0) {
-#pragma unroll
-        for (int i = 0; i < VB; i += 2) {
-            const VecT<T, 2> q = *(const FTLM_GLOBAL VecT<T, 2>*)(p + i);
-            v[i] = q.x; v[i + 1] = q.y;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < VB; ++i) v[i] = *gptr(p + i);
-    }
-}
-
-template <typename T, int VB>
-__device__ __forceinline__ void store_row(T* __restrict__ p, const T (&v)[VB]) {
-    if constexpr (sizeof(T) == 4 && VB % 4 == 0) {
-#pragma unroll
-        for (int i = 0; i < VB; i += 4) {
-            const VecT<T, 4> q = {v[i], v[i + 1], v[i + 2], v[i + 3]};
-            *(FTLM_GLOBAL VecT<T, 4>*)(p + i) = q;
-        }
-    } else if constexpr (VB % 2 == 0) {
-#pragma unroll
-        for (int i = 0; i < VB; i += 2) {
-            const VecT<T, 2> q = {v[i], v[i + 1]};
-            *(FTLM_GLOBAL VecT<T, 2>*)(p + i) = q;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < VB; ++i) *gptr(p + i) = v[i];
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ T bond_coef(const BondTable& B, int b) {
-    if constexpr (sizeof(T) == 4) return B.coef_f[b];
-    else return B.coef_d[b];
-}
 
 // Accumulates the off-diagonal terms of one row: for each antiparallel bond
 // the partner's row of x times J_b / 2; `anti` collects sum J_b / 2 over
@@ -68,10 +18,6 @@ __device__ __forceinline__ T bond_coef(const BondTable& B, int b) {
 // A partner index is in [0, D) by construction; it is clamped there anyway so
 // that a defect in the index arithmetic shows up as a parity failure and
 // never as an access outside x.
-// Fourth word of a raw buffer resource on gfx9: data format 32 bits (a zero
-// format makes every load return 0), no stride, no swizzle.
-constexpr int kBufferWord3 = 0x00020000;
-
 template <typename T, int VB, int SG = 2, bool BUF = false>
 struct GatherVisitor {
     static_assert(!BUF || VB == 1, "buffer-resource gathers serve single vectors");
@@ -233,12 +179,12 @@ template <typename L, int MODE, typename T, int VB, int EPI, bool BUF = false>
 __device__ __forceinline__ void hv_body(const SectorDev& S, const BondTable& B, const HvLds& lds,
                                         const T* __restrict__ x, T* __restrict__ y, uint64_t ld,
                                         uint32_t col0, uint32_t row0, uint32_t nrows, uint32_t bid,
-                                        uint32_t G, const T* ab, bool first, double* wsum) {
+                                        uint32_t G, int shift, const T* ab, bool first, double* wsum) {
     const Binom C{lds.binom, S.bw};
     const int wave = threadIdx.x >> 6;
     const T jsum4 = sizeof(T) == 4 ? T(B.jsum4_f) : T(B.jsum4_d);
     const uint32_t ntiles = (nrows + kBlock - 1) / kBlock;
-    for_each_tile(ntiles, bid, G, [&](uint32_t tile) {
+    for_each_tile(ntiles, bid, G, shift, [&](uint32_t tile) {
         const uint32_t r = tile * kBlock + threadIdx.x;
         const bool valid = r < nrows;
         T xt[VB], out[VB];
@@ -304,7 +250,63 @@ __global__ __launch_bounds__(kBlock) void hv_kernel(SectorDev S, BondTable B, Hv
     const HvLds lds = hv_lds_setup<MODE>(smem, S);
     __syncthreads();
     hv_body<L, MODE, T, VB, kEpiPlain, BUF>(S, Bs, lds, static_cast<const T*>(h.x), static_cast<T*>(h.y), h.ld, h.col0,
-                                        h.row0, h.nrows, blockIdx.x, gridDim.x, nullptr, false, nullptr);
+                                        h.row0, h.nrows, blockIdx.x, gridDim.x, h.super_shift, nullptr, false, nullptr);
+}
+
+// How the run kernel takes rows of a given size: rows a lane, sites of the low
+// part, rows a wave takes at a time at most, and blocks at most. Icosidodecahedron,
+// N = 30: 4-byte rows 3.0 ms with 4 rows a lane and 14 sites (2 rows 3.6, 1 row
+// 4.8; 13 sites 3.1-3.3), 8-byte rows 5.1 (2 rows, 13 sites; 14 sites 5.4-6.0),
+// 16-byte rows 7.3 (12 and 14 sites 7.5; one row a lane 8.1), 32-byte rows
+// 14.4 (12 sites, 64 rows a wave; 128 rows 15.2). Narrow rows spread over 8192
+// blocks, whose rank tables are staged once for several tiles; for wider ones
+// a block takes one tile, see hv_grid.
+struct RunShape {
+    int lane_rows, low_bits;
+    uint32_t chunk, blocks;
+};
+constexpr RunShape run_shape(size_t row_bytes) {
+    return row_bytes <= 4    ? RunShape{4, 14, 1024, 8192}
+           : row_bytes <= 8  ? RunShape{2, 13, 512, 1u << 30}
+           : row_bytes <= 16 ? RunShape{2, 13, 256, 1u << 30}
+                             : RunShape{1, 12, 64, 1u << 30};
+}
+constexpr int kRunGroup = 2;  // bonds a slot: 4 or 8 gave 3.3 and 4.1 ms for 4-byte rows, 4 8.1 for 16-byte rows
+
+// The plain H.x by runs: every wave takes `chunk` consecutive rows at a time
+// (runs.hpp), four waves a block, the blocks in for_each_tile's order.
+//
+// What bounds it. One FP32 vector at N = 30: 3.0 ms against 7.4 for the
+// row-by-row kernel, whose 1400 VALU instructions per 64 rows index every
+// row's partners on their own; by runs the high sites' share is computed once
+// per run and a partner costs a mask, a count, one LDS read and a
+// multiply-add, about 500 in all. From 16-byte rows on the lines missed in L2
+// bound it (that path gives 7 TB/s, whether the Infinity Cache holds the line
+// or not): four FP32 columns 9.4 -> 7.3 ms, eight 17.7 -> 14.4.
+template <typename L, typename T, int VB>
+__global__ __launch_bounds__(kBlock) void hv_runs_kernel(SectorDev S, BondTable B, HvLaunch h) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ BondTable Bs;
+    stage_bonds(Bs, &B);
+    const int low_bits = h.low_bits;
+    uint32_t* low = reinterpret_cast<uint32_t*>(smem);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(kLow.rank);
+    for (int i = threadIdx.x; i < (1 << low_bits) / 2; i += kBlock) low[i] = *gptr(src + i);
+    uint32_t* binom = low + (1 << low_bits) / 2;
+    stage_binomials(binom, S.binom, S.n_sites * S.bw);
+    const Binom C{binom, S.bw};
+    const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
+    const uint32_t block_rows = kWaves * h.chunk;
+    const uint32_t ntiles = uint32_t((uint64_t(h.nrows) + block_rows - 1) / block_rows);
+    for_each_tile(ntiles, blockIdx.x, gridDim.x, h.super_shift, [&](uint32_t tile) {
+        const uint64_t r0 = uint64_t(tile) * block_rows + uint64_t(wave) * h.chunk;
+        if (r0 >= h.nrows) return;
+        const uint32_t n = h.nrows - uint32_t(r0) < h.chunk ? h.nrows - uint32_t(r0) : h.chunk;
+        const uint32_t pos = h.row0 + uint32_t(r0);
+        run_rows<L, T, VB, run_shape(VB * sizeof(T)).lane_rows, kRunGroup>(S, Bs, smem, C, low_bits,
+                                                                  static_cast<const T*>(h.x), static_cast<T*>(h.y),
+                                                                  h.ld, h.col0, h.row0, pos, pos + n);
+    });
 }
 
 // The epilogue scalars [hv_a | hv_b] of columns [col0, col0 + VB), in the
@@ -385,8 +387,8 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
         __syncthreads();
         const T* x = static_cast<const T*>(sw.u[(step - 1) & 1]);
         T* y = static_cast<T*>(sw.u[step & 1]);
-        hv_body<L, MODE, T, VB, kEpiLanczos>(S, B, lds, x, y, a.ld, a.col0, 0, S.dim, local, sw.items, ab,
-                                              step == 1, wsum);
+        hv_body<L, MODE, T, VB, kEpiLanczos>(S, B, lds, x, y, a.ld, a.col0, 0, S.dim, local, sw.items,
+                                             kXcdSuperShift, ab, step == 1, wsum);
         store_partials<VB>(sw, a, wsum, local);
         __syncthreads();  // LDS (bonds, scalars, tables) is restaged by the next item
     }
@@ -397,17 +399,20 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
     }
 }
 
-// Dynamic LDS of the plain H.x at 20 and more FP32 columns: enough that two
-// workgroups fill a CU's 160 KB. Registers would allow six; with more rows in
-// flight the partner rows are evicted before their reuse (at N = 30, 20
-// columns: 74 -> 69 ms with CLT, 63 -> 58 ms with CR; 32 columns: 218 -> 187
-// ms with CLT). Narrower blocks keep the register-limited occupancy.
+// Dynamic LDS of the plain H.x at 20 and more FP32 columns: enough that three
+// workgroups fill a CU's 160 KB. With more rows in flight the partner rows are
+// evicted before their reuse (N = 30, 20 columns: 40.5 -> 38.9 ms; two
+// workgroups 44.9). Narrower blocks keep the register-limited occupancy (8
+// columns: 15.9 against 18.1 ms with the floor, 16: 31.3 against 33.6).
+// A block of up to 2^18 rows has no such choice of rows in flight.
 template <typename T, int VB>
-constexpr size_t hv_plain_lds_floor() { return (sizeof(T) == 4 && VB >= 20) ? size_t(72) * 1024 : 0; }
+size_t hv_plain_lds_floor(uint32_t dim) {
+    return (sizeof(T) == 4 && VB >= 20 && dim > (1u << 18)) ? size_t(48) * 1024 : 0;
+}
 
 template <typename L, int MODE, typename T, int VB, bool BUF = false>
 hipError_t launch_hv_one(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
-    const size_t need = hv_lds_bytes(s), floor = hv_plain_lds_floor<T, VB>();
+    const size_t need = hv_lds_bytes(s), floor = hv_plain_lds_floor<T, VB>(s.dim);
     const size_t lds = need > floor ? need : floor;
     auto kern = hv_kernel<L, MODE, T, VB, BUF>;
     if (lds > 65536) {
@@ -490,6 +495,103 @@ hipError_t with_mode(int mode, int n_sites, F&& f) {
     return f(uint32_t{}, std::integral_constant<int, kModeCr>{});
 }
 
+// Tiles per XCD super-tile (log2) of a plain H.x over `ntiles` tiles: 64 tiles
+// (24-site square lattice, 8 columns: 363 us with 16, 342 with 64, 375 with
+// 256; N = 30 within 0.3 %) or 16 (2^most), fewer where an XCD would get less
+// than 16 super-tiles (16 sites, 51 tiles: super-tiles of 16 went to four of the
+// XCDs and took 22 us, single tiles take 9).
+inline int plain_super_shift(uint64_t ntiles, int most) {
+    int s = most;
+    while (s > 0 && (ntiles >> s) < 128) --s;
+    return s;
+}
+
+// Runs of a sector whose low part has `low_bits` sites, as a double.
+inline double run_count(int n_sites, int n_up, int low_bits) {
+    double runs = 0.0, c = 1.0;  // c = C(n_sites - low_bits, a)
+    const int nh = n_sites - low_bits;
+    for (int a = 0; a <= nh && a <= n_up; ++a) {
+        if (n_up - a <= low_bits) runs += c;
+        c = c * double(nh - a) / double(a + 1);
+    }
+    return runs;
+}
+
+// Whether a product of `row_bytes` a row goes by runs. Below about a million
+// rows the row-by-row kernel's shorter start wins (N = 22, one FP32 vector: 30
+// against 40 us; N = 23: 55 against 49; N = 24: 110 against 79, and from 8- and
+// 16-byte rows on the lines lie one and two doublings higher). A run costs
+// about two passes of a wave whatever its length, so there must be rows to
+// each: sectors near half filling have 400 runs per million rows with 14 low
+// sites and twice as many per site less. With three times as many, 13 million
+// rows still gain (28 sites, 18 up, 8-byte rows 558 -> 532 us), 3 million lose
+// (26 sites, 17 up: 156 -> 290 us); above 32 sites, where the row-by-row
+// kernel walks 64-bit labels, ten times as many still pay (34 sites, 10 up:
+// 10.7 -> 7.2 ms). 32-byte rows are bound by the lines they miss either way
+// and gain only in the largest sectors (N = 30: 15.9 -> 14.4 ms, N = 28 equal);
+// wider rows do not (16 FP32 columns: 31.2 against 32.2 ms).
+inline bool by_runs(const SectorDev& s, size_t row_bytes) {
+    if (row_bytes > 32) return false;
+    const RunShape shape = run_shape(row_bytes);
+    if (s.n_sites <= shape.low_bits) return false;
+    const bool table = s.mode == kModeClt || s.mode == kModeLin;
+    const double dim = double(s.dim);
+    const double least = row_bytes <= 4 ? (table ? 4.0 : 1.25) : row_bytes <= 8 ? 2.0 : row_bytes <= 16 ? 4.0 : 64.0;
+    if (dim < least * 1048576.0) return false;
+    const double unit = double(1u << (14 - shape.low_bits)) * 500e-6 * dim;  // 500 per million rows at 14 sites
+    const double runs = run_count(s.n_sites, s.n_up, shape.low_bits);
+    if (runs <= unit) return true;
+    if (row_bytes > 16) return false;
+    if (s.n_sites > 32 && dim >= 67108864.0) return runs <= (row_bytes <= 8 ? 10.0 : 5.0) * unit;
+    return row_bytes <= 8 && dim >= 12582912.0 && runs <= 4.0 * unit;
+}
+
+template <typename L, typename T, int VB>
+hipError_t launch_hv_runs(const SectorDev& s, const BondTable& B, HvLaunch h, hipStream_t st) {
+    constexpr RunShape shape = run_shape(VB * sizeof(T));
+    constexpr uint32_t kStep = 64u * uint32_t(shape.lane_rows);
+    h.low_bits = shape.low_bits;
+    // Fewer rows a wave where 8192 waves would not all get some, and where
+    // short runs lie together and a wave with many of them would end last (28
+    // sites, 18 up, one FP32 vector: 1024 rows a wave 570 us, 256 rows 413).
+    uint32_t steps = h.nrows / (8192u * kStep);
+    steps = steps < 1 ? 1 : steps > shape.chunk / kStep ? shape.chunk / kStep : steps;
+    if (run_count(s.n_sites, s.n_up, shape.low_bits) > 600e-6 * double(1u << (14 - shape.low_bits)) * double(s.dim))
+        steps = steps < 256u / kStep ? steps : 256u / kStep;
+    h.chunk = steps * kStep;
+    const uint64_t blocks = (uint64_t(h.nrows) + kWaves * h.chunk - 1) / (uint64_t(kWaves) * h.chunk);
+    h.grid = int(blocks < 8 ? blocks : blocks < shape.blocks ? (blocks + 7) & ~uint64_t(7) : shape.blocks);
+    h.super_shift = plain_super_shift(blocks, 6);
+    const size_t lds = (size_t(2) << h.low_bits) + size_t(s.n_sites) * size_t(s.bw) * 4;
+    hipLaunchKernelGGL((hv_runs_kernel<L, T, VB>), dim3(unsigned(h.grid)), dim3(kBlock), lds, st, s, B, h);
+    return hipGetLastError();
+}
+
+// The index map that the row-by-row kernel uses in a sector that holds one:
+// its own while latency counts and for rows of up to 8 bytes, where a lookup
+// is shorter than the ranking walk (N = 18, 8 FP32 columns: compressed table 20
+// us, ranking 26; N = 23, one column: 40 against 55), the ranking from 2^18
+// rows on for wider rows, where the table's loads come on top of the rows' (N
+// = 26, 17 up, 8 columns: 308 against 271 us; N = 30: 22.4 against 15.9 ms) and
+// in place of the full table at any width (N = 26, 17 up, one column: 301
+// against 146 us).
+inline int product_map(const SectorDev& s, size_t row_bytes) {
+    const bool rank = s.dim >= (1u << 18) && (row_bytes > 8 || s.mode == kModeFull);
+    return rank ? kModeCr : s.mode;
+}
+
+// Blocks of the row-by-row kernel. Rows of up to 16 bytes: a persistent grid of
+// at most 2048 (latency-bound; one block per tile, whose tables are staged each
+// time, gave 8.0 against 7.4 ms at one column). Wider rows are bound by the
+// lines they miss in L2, and a block takes one tile: blocks are dispatched in
+// order, so the rows in flight stay one compact front, where the blocks of a
+// persistent grid drift apart and share fewer partner rows. N = 30, FP32: 8
+// columns 17.7 -> 15.9 ms, 12 28.9 -> 23.7, 16 42.0 -> 31.2, 20 55.4 -> 38.9,
+// 4 FP64 columns 19.5 -> 14.8.
+inline uint32_t hv_grid(uint32_t nrows, size_t row_bytes) {
+    return row_bytes <= 16 ? rows_grid(nrows) : capped_grid(nrows, 1u << 30);
+}
+
 // A single contiguous vector of fewer than 2^32 bytes takes the
 // buffer-resource gathers (GatherVisitor, BUF) with CR and the compressed
 // table. N = 30, one FP32 vector: CR 7.77 -> 7.37 ms, CLT 6.06 -> 5.90; FP64
@@ -497,15 +599,34 @@ hipError_t with_mode(int mode, int n_sites, F&& f) {
 // unchanged, so they keep the pointer form; reading the compressed table
 // through a buffer as well changed nothing.
 template <typename T>
-hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
+hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
+    const size_t row_bytes = size_t(h0.vb) * sizeof(T);
+    HvLaunch h = h0;
+    if (by_runs(s, row_bytes)) {
+        auto go = [&](auto vb) {
+            constexpr int VB = decltype(vb)::value;
+            return s.n_sites > 32 ? launch_hv_runs<uint64_t, T, VB>(s, B, h, st)
+                                  : launch_hv_runs<uint32_t, T, VB>(s, B, h, st);
+        };
+        if (h.vb == 1) return go(std::integral_constant<int, 1>{});
+        if (h.vb == 2) return go(std::integral_constant<int, 2>{});
+        if (h.vb == 4) return go(std::integral_constant<int, 4>{});
+        if constexpr (sizeof(T) == 4)
+            if (h.vb == 8) return go(std::integral_constant<int, 8>{});
+    }
+    h.grid = int(hv_grid(h.nrows, row_bytes));
+    h.super_shift = plain_super_shift((uint64_t(h.nrows) + kBlock - 1) / kBlock, row_bytes <= 16 ? 4 : 6);
+    const int mode = product_map(s, row_bytes);
     const bool buf = h.vb == 1 && h.ld == 1 && h.col0 == 0 && uint64_t(s.dim) * sizeof(T) < (uint64_t(1) << 32) &&
-                     (s.mode == kModeCr || s.mode == kModeClt);
-    return with_mode(s.mode, s.n_sites, [&](auto l, auto m) {
+                     (mode == kModeCr || mode == kModeClt);
+    SectorDev sm = s;
+    sm.mode = mode;
+    return with_mode(mode, s.n_sites, [&](auto l, auto m) {
         using L = decltype(l);
         constexpr int MODE = decltype(m)::value;
         if constexpr (std::is_same_v<L, uint32_t> && (MODE == kModeCr || MODE == kModeClt))
-            if (buf) return launch_hv_one<L, MODE, T, 1, true>(s, B, h, st);
-        return with_vb<T>(h.vb, [&](auto vb) { return launch_hv_one<L, MODE, T, decltype(vb)::value>(s, B, h, st); });
+            if (buf) return launch_hv_one<L, MODE, T, 1, true>(sm, B, h, st);
+        return with_vb<T>(h.vb, [&](auto vb) { return launch_hv_one<L, MODE, T, decltype(vb)::value>(sm, B, h, st); });
     });
 }
 

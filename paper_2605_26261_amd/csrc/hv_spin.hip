@@ -194,7 +194,7 @@ __device__ __forceinline__ void hv_spin_body(const SectorDev& S, const BondTable
                                              bool first, double* wsum) {
     const int wave = threadIdx.x >> 6;
     const uint32_t ntiles = (nrows + kBlock - 1) / kBlock;
-    for_each_tile(ntiles, bid, G, [&](uint32_t tile) {
+    for_each_tile(ntiles, bid, G, kXcdSuperShift, [&](uint32_t tile) {
         const uint32_t r = tile * kBlock + threadIdx.x;
         const bool valid = r < nrows;
         T xt[VB], out[VB];
@@ -437,7 +437,9 @@ __global__ __launch_bounds__(kBlock) void neighbors_spin_kernel(SectorDev S, Bon
 
 }  // namespace
 
-hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
+hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
+    HvLaunch h = h0;
+    h.grid = int(rows_grid(h.nrows));
     const size_t lds = hv_spin_lds_bytes(s);
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);

@@ -90,7 +90,10 @@ struct HvLaunch {
     uint32_t nrows;
     int vb;
     int dtype;
-    int grid;
+    int grid;        // set by the launcher, as the rest
+    int super_shift;
+    int low_bits;    // run kernel: sites of a run's low part
+    uint32_t chunk;  // run kernel: rows a wave takes at a time
 };
 
 // One sector of a Lanczos launch (one sector, all sectors of a plan, or the

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
 #pragma unroll
     for (int c = 0; c < CB; ++c) part[c] = 0.0;
     const uint32_t ntiles = (dim + kBlock - 1) / kBlock;
-    for_each_tile(ntiles, local, sw.G, [&](uint32_t tile) {
+    for_each_tile(ntiles, local, sw.G, kXcdSuperShift, [&](uint32_t tile) {
         const uint32_t t = tile * kBlock + threadIdx.x;
         if (t >= dim) return;
         const uint64_t i = t;

@@ -33,29 +33,29 @@ __device__ __forceinline__ void for_each_span_tile(uint32_t ntiles, uint32_t bid
     for (uint32_t tile = sp.first; tile < sp.end; tile += sp.step) f(tile);
 }
 
-// Tiles per XCD super-tile in the gather kernels' schedule (for_each_tile).
-constexpr uint32_t kXcdSuperTile = 16;
+// Tiles per XCD super-tile (log2) in the schedule of the kernels that reduce
+// (for_each_tile): fixed, because it fixes the order of their sums.
+constexpr int kXcdSuperShift = 4;
 
 // Calls f(tile) for the tiles of block `bid` (the gather kernels and the
 // start vectors). With G a multiple of 8, the tiles are dealt to the XCDs
-// in super-tiles of kXcdSuperTile tiles (4096 rows), round-robin: super-tile
-// k belongs to XCD k mod 8, and inside its super-tiles an XCD's blocks
-// stride by G / 8 tiles. All eight XCDs thus sweep one common front of the
+// in super-tiles of 2^shift tiles, round-robin:
+// super-tile k belongs to XCD k mod 8, and inside its super-tiles an XCD's
+// blocks stride by G / 8 tiles. All eight XCDs thus sweep one common front of the
 // rows, so the partner rows that miss one XCD's L2 are fetched into the
 // shared Infinity Cache once for all of them. Contiguous eighths of the rows
 // per XCD were slower at every width (N = 30, CR Lanczos step at 12 columns:
 // 38.0 ms against 34.5; super-tiles of 1 to 16 tiles within 1 %, 128 tiles
 // 35.7 ms).
 template <typename F>
-__device__ __forceinline__ void for_each_tile(uint32_t ntiles, uint32_t bid, uint32_t G, F&& f) {
+__device__ __forceinline__ void for_each_tile(uint32_t ntiles, uint32_t bid, uint32_t G, int shift, F&& f) {
     if (G >= 8 && (G & 7u) == 0) {
-        constexpr uint32_t S = kXcdSuperTile;
         const uint32_t xcd = bid & 7u, slot = bid >> 3, per = G >> 3;
-        const uint32_t supers = (ntiles + S - 1u) / S;
+        const uint32_t supers = (ntiles + (1u << shift) - 1u) >> shift;
         const uint32_t mine = supers > xcd ? (supers - xcd + 7u) / 8u : 0u;  // super-tiles of this XCD
-        const uint32_t count = mine * S;
+        const uint32_t count = mine << shift;
         for (uint32_t q = slot; q < count; q += per) {
-            const uint32_t tile = (xcd + 8u * (q / S)) * S + q % S;
+            const uint32_t tile = ((xcd + 8u * (q >> shift)) << shift) + (q & ((1u << shift) - 1u));
             if (tile < ntiles) f(tile);
         }
     } else {

@@ -40,7 +40,8 @@ LAUNCH_WIDTHS_F32 = (1, 2, 4, 8, 10, 12, 16, 20, 32)
 # counters (profiles/hv_lanczos_n30_r20_counters.md). The memory side
 # includes the Infinity Cache, so this bounds the HBM traffic from above.
 # They describe the kernel sources with this hash and are dropped otherwise.
-KERNEL_SOURCES = ["layout.hpp", "device.hpp", "kernels.hpp", "rowloop.hpp", "hv_impl.hpp", "hv_f32.hip"]
+KERNEL_SOURCES = ["layout.hpp", "device.hpp", "kernels.hpp", "rowloop.hpp", "rowio.hpp", "lowtab.hpp", "runs.hpp",
+                  "hv_impl.hpp", "hv_f32.hip"]
 MEASURED_TRAFFIC = {"sources": "1123cd4f9861cbbe", "bytes": {
     "clt": {1: 19.44e9, 2: 34.19e9, 4: 65.48e9, 8: 125.77e9, 10: 160.94e9, 12: 197.3e9, 16: 272.91e9, 20: 340.19e9},
     "cr": {1: 13.41e9, 2: 26.88e9, 4: 55.84e9, 8: 112.51e9, 10: 153.01e9, 12: 190.25e9, 16: 250.94e9, 20: 338.26e9},

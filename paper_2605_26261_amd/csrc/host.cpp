@@ -114,7 +114,8 @@ size_t layout_state(uint64_t dim, int R, int dtype, size_t off, SectorState& st)
     const size_t es = dtype == FTLM_F32 ? 4 : 8;
     st.u0 = off; off = align256(off + size_t(dim) * size_t(R) * es);
     st.u1 = off; off = align256(off + size_t(dim) * size_t(R) * es);
-    const size_t slots = std::max(stream_grid(uint32_t(dim)), sector_items(uint32_t(dim)));
+    size_t slots = std::max(stream_grid(uint32_t(dim)), strided_items(uint32_t(dim)));
+    if (dtype == FTLM_F32) slots = std::max(slots, size_t(sector_items(uint32_t(dim), true)));
     st.partials = off; off = align256(off + slots * size_t(R) * sizeof(double));
     st.chains = off; off = align256(off + size_t(R) * sizeof(Chain));
     st.alpha = off; off = align256(off + size_t(R) * kMaxSteps * sizeof(double));
@@ -132,7 +133,7 @@ size_t layout_state(uint64_t dim, int R, int dtype, size_t off, SectorState& st)
 // in the caller's labels. The descriptor array goes to `dev_secs`
 // (device). Blocks of the static-grid kernels: each sector gets stream_grid(D)
 // blocks starting at a multiple of 8; the persistent H.x splits it into
-// sector_items(D) work items.
+// sector_items() work items.
 void job_layout(LanczosJob& job, const std::vector<SectorDev>& devs, const std::vector<SectorState>& states,
                 void* base, int R, int M, int dtype, SecWork* dev_secs, const std::vector<const ftlm_graph*>& graphs,
                 const std::vector<BondTable*>& dev_tables, const std::vector<int>& graph_of) {
@@ -173,7 +174,7 @@ void job_layout(LanczosJob& job, const std::vector<SectorDev>& devs, const std::
         w.keys = at<uint64_t>(base, st.keys);
         job.key_ptrs.push_back(at<uint64_t>(base, st.keys));
         w.G = stream_grid(devs[i].dim);
-        w.items = sector_items(devs[i].dim);
+        w.items = sector_items(devs[i].dim, block_items(job.two_s, dtype));
         items += w.items;
         w.block0 = block;
         block = (block + w.G + 7) & ~7u;

@@ -152,7 +152,12 @@ struct LanczosJob {
         a.nsec = nsec;
         a.grid = grid;
         a.items = items;
-        for (const SecWork& w : secs) a.max_dim = std::max<uint64_t>(a.max_dim, w.S.dim);
+        for (const SecWork& w : secs) {
+            a.max_dim = std::max<uint64_t>(a.max_dim, w.S.dim);
+            a.xcd_items += int(xcd_items(w.items, 0));
+            a.xcd_pairs += int(xcd_items((w.items + 1) / 2, 0));
+        }
+        a.n_up = secs.empty() ? 0 : secs[0].S.n_up;
         a.ld = uint64_t(R);
         a.dtype = dtype;
         // FP32 vectors: an exact invariant subspace leaves a residual of about

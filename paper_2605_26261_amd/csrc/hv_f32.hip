@@ -1,8 +1,8 @@
-// FP32 instantiations of the H.x kernels.
+// FP32 instantiations of the plain H.x kernels.
 #include "hv_impl.hpp"
 
 namespace ftlm {
-template hipError_t launch_hv_typed<float>(const SectorDev&, const BondTable&, const HvLaunch&, hipStream_t);
-template hipError_t launch_lanczos_typed<float>(int, int, const LanczosLaunch&, size_t,
-                                                hipStream_t);
+hipError_t launch_hv_f32(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
+    return launch_hv_typed<float>(s, B, h, st);
+}
 }  // namespace ftlm

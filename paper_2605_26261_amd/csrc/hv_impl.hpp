@@ -188,6 +188,9 @@ __device__ __forceinline__ void hv_body(const SectorDev& S, const BondTable& B, 
         const uint32_t r = tile * kBlock + threadIdx.x;
         const bool valid = r < nrows;
         T xt[VB], out[VB];
+        double p[VB];
+#pragma unroll
+        for (int c = 0; c < VB; ++c) p[c] = 0.0;
         if (valid) {
             const uint32_t t = row0 + r;
             T acc[VB];
@@ -205,26 +208,11 @@ __device__ __forceinline__ void hv_body(const SectorDev& S, const BondTable& B, 
 #pragma unroll
             for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];
             T* yrow = y + uint64_t(r) * ld + col0;
-            if constexpr (EPI == kEpiLanczos) {
-                T z[VB];
-                if (!first) {
-                    load_row<T, VB>(yrow, z);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < VB; ++c) z[c] = T(0);
-                }
-#pragma unroll
-                for (int c = 0; c < VB; ++c) {
-                    out[c] = ab[c] * out[c] - ab[VB + c] * z[c];
-                }
-            }
+            if constexpr (EPI == kEpiLanczos) lanczos_epilogue<T, VB>(xt, out, yrow, ab, first, p);
             store_row<T, VB>(yrow, out);
         }
         if constexpr (EPI == kEpiLanczos) {
             // every lane takes part; rows past the end add 0
-            double p[VB];
-#pragma unroll
-            for (int c = 0; c < VB; ++c) p[c] = valid ? double(xt[c]) * double(out[c]) : 0.0;
             wave_fold_columns<VB>(p, wsum + wave * VB);
         }
     });
@@ -236,10 +224,10 @@ __device__ __forceinline__ void hv_body(const SectorDev& S, const BondTable& B, 
 // arguments or through a generic pointer, the table costs scalar or flat
 // loads whose waits serialise the gathers). Visible after the caller's next
 // barrier.
-__device__ __forceinline__ void stage_bonds(BondTable& dst, const BondTable* src) {
+__device__ __forceinline__ void stage_bonds(BondTable& dst, const BondTable* src, int threads = kBlock) {
     uint32_t* d = reinterpret_cast<uint32_t*>(&dst);
     const uint32_t* w = reinterpret_cast<const uint32_t*>(src);
-    for (int i = threadIdx.x; i < int(sizeof(BondTable) / 4); i += kBlock) d[i] = *gptr(w + i);
+    for (int i = threadIdx.x; i < int(sizeof(BondTable) / 4); i += threads) d[i] = *gptr(w + i);
 }
 
 template <typename L, int MODE, typename T, int VB, bool BUF = false>
@@ -335,10 +323,10 @@ __device__ __forceinline__ void store_partials(const SecWork& sw, const LanczosL
 
 // alpha_k of the launch's columns of one sector from its n partial slots, one
 // thread per column.
-template <int VB>
+template <int VB, int NT = kBlock, int SPAN = NT>
 __device__ __forceinline__ void finish_alpha(const SecWork& sw, const LanczosLaunch& a, uint32_t n, double* red) {
-    __shared__ double tot[grid_sum_slots<VB>()];
-    grid_sum_cols<VB>(sw.partials, int(n), int(a.ld), int(a.col0), VB, red, tot);
+    __shared__ double tot[grid_sum_slots<VB, NT>()];
+    grid_sum_cols<VB, NT, SPAN>(sw.partials, int(n), int(a.ld), int(a.col0), VB, red, tot);
     if (threadIdx.x < VB) {
         Chain* ch = &sw.chains[a.col0 + threadIdx.x];
         const double alpha = ch->s_cur * tot[threadIdx.x], up = alpha * ch->s_cur;
@@ -372,22 +360,23 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
         if (threadIdx.x == 0) next = atomicAdd(a.queue + xcd, 1u);
         __syncthreads();
         uint32_t local = 0;
-        const int s = queue_item(secs, a.nsec, xcd, next, &local);
+        const int s = uniform(queue_item(secs, a.nsec, xcd, next, &local));
         __syncthreads();  // every thread has read `next`
         if (s < 0) break;
+        local = uniform(local);
         const SecWork& sw = secs[s];
-        if (sw.state[1] == 0) continue;
-        const int step = sw.state[0];
-        const SectorDev S = sw.S;
+        if (uniform(sw.state[1]) == 0) continue;
+        const int step = uniform(sw.state[0]);
+        const SectorDev S = uniform(sw.S);
         stage_bonds(B, sw.bonds);
         stage_epilogue<T, VB>(ab, sw.chains + a.col0);
         const HvLds lds = hv_lds_setup<MODE>(smem, S);
         double* wsum = lds.red;
         for (int i = threadIdx.x; i < kWaves * VB; i += kBlock) wsum[i] = 0.0;
         __syncthreads();
-        const T* x = static_cast<const T*>(sw.u[(step - 1) & 1]);
-        T* y = static_cast<T*>(sw.u[step & 1]);
-        hv_body<L, MODE, T, VB, kEpiLanczos>(S, B, lds, x, y, a.ld, a.col0, 0, S.dim, local, sw.items,
+        const T* x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
+        T* y = uniform(static_cast<T*>(sw.u[step & 1]));
+        hv_body<L, MODE, T, VB, kEpiLanczos>(S, B, lds, x, y, a.ld, a.col0, 0, S.dim, local, uniform(sw.items),
                                              kXcdSuperShift, ab, step == 1, wsum);
         store_partials<VB>(sw, a, wsum, local);
         __syncthreads();  // LDS (bonds, scalars, tables) is restaged by the next item
@@ -395,7 +384,7 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
     if (queue_exit(a.queue, gridDim.x, &flag)) {
         double* red = reinterpret_cast<double*>(smem);
         for (int s = 0; s < a.nsec; ++s)
-            if (secs[s].state[1] != 0) finish_alpha<VB>(secs[s], a, secs[s].items, red);
+            if (uniform(secs[s].state[1]) != 0) finish_alpha<VB>(secs[s], a, secs[s].items, red);
     }
 }
 
@@ -427,25 +416,11 @@ hipError_t launch_hv_one(const SectorDev& s, const BondTable& B, const HvLaunch&
 // Grid of a persistent launch: the resident workgroups of the kernel at this
 // LDS size (a multiple of 8, so every XCD gets the same number), capped at
 // the number of work items.
-hipError_t persistent_grid(const void* kern, size_t lds, int items, int* grid);
-
-// Dynamic LDS of the Lanczos H.x that holds CR at 8 and 16 FP32 columns to
-// three workgroups per CU (their registers allow four) when the vector
-// block of the largest sector does not fit the 256 MB Infinity Cache: fewer
-// rows in flight keep more of the partner rows cached. N = 30 Lanczos step:
-// 8 columns 23.0 -> 22.2 ms, 16 columns 50.9 -> 47.0 ms; the same floor made
-// 10 and 12 columns and every CLT width slower.
-template <int MODE, typename T, int VB>
-size_t lanczos_lds_floor(uint64_t max_dim) {
-    const bool big = max_dim * uint64_t(VB) * sizeof(T) > (uint64_t(256) << 20);
-    return (MODE == kModeCr && sizeof(T) == 4 && (VB == 8 || VB == 16) && big) ? size_t(48) * 1024 : 0;
-}
+hipError_t persistent_grid(const void* kern, int threads, size_t lds, int items, int* grid);
 
 template <typename L, int MODE, typename T, int VB>
 hipError_t launch_lanczos_one(const LanczosLaunch& a, size_t lds, hipStream_t st) {
     auto kern = hv_lanczos_kernel<L, MODE, T, VB>;
-    const size_t floor = lanczos_lds_floor<MODE, T, VB>(a.max_dim);
-    if (lds < floor) lds = floor;
     if (lds < kGridSumLds) lds = kGridSumLds;  // the final sums reuse the block's LDS
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -454,7 +429,7 @@ hipError_t launch_lanczos_one(const LanczosLaunch& a, size_t lds, hipStream_t st
     }
     if (!a.queue || a.items <= 0) return hipErrorInvalidValue;  // the queue counters are required
     int grid = 0;
-    hipError_t e = persistent_grid(reinterpret_cast<const void*>(kern), lds, a.items, &grid);
+    hipError_t e = persistent_grid(reinterpret_cast<const void*>(kern), kBlock, lds, a.items, &grid);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kBlock), lds, st, a);
     return hipGetLastError();

@@ -261,22 +261,23 @@ __global__ __launch_bounds__(kBlock) void hv_spin_lanczos_kernel(LanczosLaunch a
         if (threadIdx.x == 0) next = atomicAdd(a.queue + xcd, 1u);
         __syncthreads();
         uint32_t local = 0;
-        const int s = queue_item(secs, a.nsec, xcd, next, &local);
+        const int s = uniform(queue_item(secs, a.nsec, xcd, next, &local));
         __syncthreads();  // every thread has read `next`
         if (s < 0) break;
+        local = uniform(local);
         const SecWork& sw = secs[s];
-        if (sw.state[1] == 0) continue;
-        const int step = sw.state[0];
-        const SectorDev S = sw.S;
+        if (uniform(sw.state[1]) == 0) continue;
+        const int step = uniform(sw.state[0]);
+        const SectorDev S = uniform(sw.S);
         stage_bonds(B, sw.bonds);
         stage_epilogue<T, VB>(ab, sw.chains + a.col0);
         const SpinLds l = spin_lds_setup<MODE>(smem, S);
         double* wsum = l.red;
         for (int i = threadIdx.x; i < kWaves * VB; i += kBlock) wsum[i] = 0.0;
         __syncthreads();
-        const T* x = static_cast<const T*>(sw.u[(step - 1) & 1]);
-        T* y = static_cast<T*>(sw.u[step & 1]);
-        hv_spin_body<MODE, T, VB, kEpiLanczos>(S, B, l, x, y, a.ld, a.col0, 0, S.dim, local, sw.items, ab,
+        const T* x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
+        T* y = uniform(static_cast<T*>(sw.u[step & 1]));
+        hv_spin_body<MODE, T, VB, kEpiLanczos>(S, B, l, x, y, a.ld, a.col0, 0, S.dim, local, uniform(sw.items), ab,
                                                step == 1, wsum);
         store_partials<VB>(sw, a, wsum, local);
         __syncthreads();  // LDS (bonds, scalars, tables) is restaged by the next item
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(kBlock) void hv_spin_lanczos_kernel(LanczosLaunch a
     if (queue_exit(a.queue, gridDim.x, &flag)) {
         double* red = reinterpret_cast<double*>(smem);
         for (int s = 0; s < a.nsec; ++s)
-            if (secs[s].state[1] != 0) finish_alpha<VB>(secs[s], a, secs[s].items, red);
+            if (uniform(secs[s].state[1]) != 0) finish_alpha<VB>(secs[s], a, secs[s].items, red);
     }
 }
 
@@ -469,7 +470,7 @@ hipError_t launch_hv_lanczos_spin(const LanczosLaunch& a, size_t lds, hipStream_
             hipError_t e = allow_lds(kern, bytes);
             if (e != hipSuccess) return e;
             int grid = 0;
-            e = persistent_grid(reinterpret_cast<const void*>(kern), bytes, a.items, &grid);
+            e = persistent_grid(reinterpret_cast<const void*>(kern), kBlock, bytes, a.items, &grid);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kBlock), bytes, st, a);
             return hipGetLastError();

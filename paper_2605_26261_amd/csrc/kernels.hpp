@@ -100,9 +100,9 @@ struct HvLaunch {
 // active requests of a server round), in device memory. In the kernels with a
 // static grid (start vectors, update) its blocks are [block0, block0 + G) of
 // the launch grid, with G = stream_grid(D); the persistent Lanczos H.x
-// kernels (spin 1/2 and general spin) split it into `items` =
-// sector_items(D) work items. Both depend on D only, and so does the reduction order of every
-// column. Each sector carries its own bond table and step counter, so
+// kernels split it into `items` = sector_items(D, block_items(2s, dtype)) work
+// items. For vectors of one type both depend on D only, and so does the
+// reduction order of every column. Each sector carries its own bond table and step counter, so
 // sectors of different graphs at different Lanczos steps can share a launch.
 struct SecWork {
     SectorDev S;
@@ -140,6 +140,12 @@ struct LanczosLaunch {
     int mode;            // index mode shared by the sectors (host dispatch)
     int n_sites;         // N shared by the sectors (host dispatch)
     int two_s;           // local spin 2s shared by the sectors (host dispatch)
+    int n_up;            // of the first sector (host dispatch)
+    int xcd_items;       // consecutive one-slot items of XCD 0, which has the most (host launch)
+    int xcd_pairs;       // the same for two-slot items (host launch)
+    int low_bits;        // by runs: sites of a run's low part (set by the launcher)
+    int item_log;        // slots of a consecutive item, log2 (set by the launcher)
+    int one_round;       // the grid has a workgroup for every item (set by the launcher)
     // Work queue of the persistent H.x launch (kQueueWords counters, zero
     // between launches), or null for a grid of one block per work item.
     uint32_t* queue;
@@ -152,6 +158,10 @@ constexpr int kQueueWords = 9;
 constexpr size_t kQueueBytes = 256;
 
 hipError_t launch_hv(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st);
+hipError_t launch_hv_f32(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st);
+hipError_t launch_hv_f64(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st);
+hipError_t launch_lanczos_f32(const LanczosLaunch& a, hipStream_t st);
+hipError_t launch_lanczos_f64(const LanczosLaunch& a, size_t lds, hipStream_t st);
 // General-spin sectors (two_s > 1; hv_spin.hip).
 hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st);
 hipError_t launch_hv_lanczos_spin(const LanczosLaunch& a, size_t lds, hipStream_t st);
@@ -224,20 +234,67 @@ __host__ __device__ inline uint32_t rows_grid(uint32_t nrows) { return capped_gr
 // with 384 and 55.9 with 256 (one column alone was 2 % slower at 512).
 __host__ __device__ inline uint32_t stream_grid(uint32_t nrows) { return capped_grid(nrows, 512); }
 
-// Work items of a sector in the persistent Lanczos H.x, each with its own
-// slot of reduction partials: a multiple of 8 (an equal count per XCD), about
-// four row tiles per item, at most 16384. A workgroup runs several items, so
-// with many small items every workgroup ends within about one item of the
-// others whatever the kernel's occupancy; the count depends on the row count
-// only, so the reduction order, and every result, does not depend on the
+// Work items of a sector in the persistent Lanczos H.x of FP64 vectors and of
+// general spin, each with its own slot of reduction partials: a multiple of 8
+// (an equal count per XCD), about four row tiles per item, at most 16384, the
+// tiles of an item spread over its XCD's rows. The count depends on the row
+// count only, so the reduction order, and every result, does not depend on the
 // launch width, the index map or the other sectors.
-__host__ __device__ inline uint32_t sector_items(uint32_t nrows) {
+__host__ __device__ inline uint32_t strided_items(uint32_t nrows) {
     const uint32_t tiles = (nrows + kBlock - 1) / kBlock;
     if (tiles < 8) return tiles == 0 ? 1u : tiles;
     const uint32_t cap = 16384;
     uint32_t g = (tiles + 3) / 4;
     g = g < 8 ? 8 : (g < cap ? g : cap);
     return (g + 7) & ~7u;
+}
+
+// Consecutive rows to a slot of reduction partials in the Lanczos H.x of FP32
+// vectors (spin 1/2): short ones leave a small sector enough work items, and
+// the widest blocks the most compact front of rows in flight (24-site square
+// lattice, 16 columns, a slot per item: 1.13 ms with 1024 rows, 0.93 with 512);
+// 1024 beyond 2^24 rows, where shorter ones gained 1 % and the partials of a
+// workspace would grow past a thousandth of its vectors.
+__host__ __device__ inline uint32_t slot_rows(uint32_t dim) {
+    return dim <= (1u << 17) ? 256u : dim <= (1u << 24) ? 512u : 1024u;
+}
+// Slots of a sector: of consecutive rows where `block_items` (FP32, spin 1/2),
+// else one to each strided work item.
+__host__ __device__ inline bool block_items(int two_s, int dtype) { return two_s <= 1 && dtype == 0; }
+__host__ __device__ inline uint32_t sector_items(uint32_t dim, bool blocks) {
+    return blocks ? uint32_t((uint64_t(dim) + slot_rows(dim) - 1) / slot_rows(dim)) : strided_items(dim);
+}
+
+// Items per XCD super-tile (log2) in the order of consecutive items: 16, fewer
+// where an XCD would get less than 16 super-tiles.
+__host__ __device__ inline int item_shift(uint32_t items) {
+    int s = 4;
+    while (s > 0 && (items >> s) < 128u) --s;
+    return s;
+}
+// Items that XCD x takes of a sector's consecutive items, the ones past the
+// sector's end in the last super-tile included.
+__host__ __device__ inline uint32_t xcd_items(uint32_t items, uint32_t xcd) {
+    const int sh = item_shift(items);
+    const uint32_t supers = (items + (1u << sh) - 1u) >> sh;
+    return (supers > xcd ? (supers - xcd + 7u) / 8u : 0u) << sh;
+}
+
+// Work item k of XCD x over the sectors' consecutive items of 2^item_log slots,
+// sector by sector: the sector and *local (past the sector's items in its last
+// super-tile), or -1 when the XCD's items are exhausted.
+__device__ __forceinline__ int block_item(const SecWork* secs, int nsec, uint32_t xcd, uint32_t k, int item_log,
+                                          uint32_t* local) {
+    for (int s = 0; s < nsec; ++s) {
+        const uint32_t items = (secs[s].items + (1u << item_log) - 1u) >> item_log, cnt = xcd_items(items, xcd);
+        if (k < cnt) {
+            const int sh = item_shift(items);
+            *local = ((xcd + 8u * (k >> sh)) << sh) + (k & ((1u << sh) - 1u));
+            return s;
+        }
+        k -= cnt;
+    }
+    return -1;
 }
 
 // Work item k of XCD x in a persistent launch: the sectors' items whose

@@ -13,10 +13,7 @@
 
 namespace ftlm {
 
-template <typename T>
-hipError_t launch_lanczos_typed(int, int, const LanczosLaunch&, size_t, hipStream_t);
-
-hipError_t persistent_grid(const void* kern, size_t lds, int items, int* grid) {
+hipError_t persistent_grid(const void* kern, int threads, size_t lds, int items, int* grid) {
     static std::mutex mu;
     static std::map<std::pair<const void*, size_t>, int> cache;  // per kernel and LDS size
     int per_cu = 0;
@@ -26,7 +23,7 @@ hipError_t persistent_grid(const void* kern, size_t lds, int items, int* grid) {
         if (it != cache.end()) {
             per_cu = it->second;
         } else {
-            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBlock, lds);
+            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds);
             if (e != hipSuccess) return e;
             cache[{kern, lds}] = per_cu;
         }
@@ -43,8 +40,7 @@ hipError_t persistent_grid(const void* kern, size_t lds, int items, int* grid) {
 
 hipError_t launch_hv_lanczos(const LanczosLaunch& a, size_t lds, hipStream_t st) {
     if (a.two_s > 1) return launch_hv_lanczos_spin(a, lds, st);
-    return a.dtype == 0 ? launch_lanczos_typed<float>(a.mode, a.n_sites, a, lds, st)
-                        : launch_lanczos_typed<double>(a.mode, a.n_sites, a, lds, st);
+    return a.dtype == 0 ? launch_lanczos_f32(a, st) : launch_lanczos_f64(a, lds, st);
 }
 
 namespace {

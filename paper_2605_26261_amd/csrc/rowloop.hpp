@@ -184,29 +184,32 @@ __device__ __forceinline__ bool queue_exit(uint32_t* q, uint32_t grid, int* flag
 }
 
 // Columns that grid_sum_cols reduces together, and the LDS it needs for them.
-template <int VB>
-__host__ __device__ constexpr int grid_sum_group() { return VB < 8 ? VB : 8; }
-template <int VB>
-__host__ __device__ constexpr size_t grid_sum_lds() { return sizeof(double) * 128 * size_t(grid_sum_group<VB>()); }
-constexpr size_t kGridSumLds = sizeof(double) * 128 * 8;  // at every width
-template <int VB>
+template <int VB, int NT = kBlock>
+__host__ __device__ constexpr int grid_sum_group() { return VB < 2048 / NT ? VB : 2048 / NT; }
+template <int VB, int NT = kBlock>
+__host__ __device__ constexpr size_t grid_sum_lds() {
+    return sizeof(double) * (NT / 2) * size_t(grid_sum_group<VB, NT>());
+}
+constexpr size_t kGridSumLds = sizeof(double) * 1024;  // at every width
+template <int VB, int NT = kBlock>
 __host__ __device__ constexpr int grid_sum_slots() {
-    return (VB + grid_sum_group<VB>() - 1) / grid_sum_group<VB>() * grid_sum_group<VB>();
+    return (VB + grid_sum_group<VB, NT>() - 1) / grid_sum_group<VB, NT>() * grid_sum_group<VB, NT>();
 }
 
 // Fixed-order sums over the G block partials of the columns col0 .. col0 +
-// nc - 1 (nc <= VB), partials[g * pstride + col]: thread i sums blocks i,
-// i + kBlock, ..., then the block combines the threads as a tree over i, i +
-// 128, i + 64, ..., i + 1, so the order depends on G only. Up to eight columns
-// go through the tree together: two exchanges through LDS, then the fold of
-// the first wave, where one column at a time took eight barriers each (the
-// Lanczos H.x over 924 rows of 8 FP64 columns: 17.6 -> 11.8 us). tot[c] (LDS, grid_sum_slots<VB>() doubles)
-// receives the totals, visible to the first wave; red holds grid_sum_lds<VB>()
-// bytes of LDS.
-template <int VB>
+// nc - 1 (nc <= VB), partials[g * pstride + col]: thread i of NT sums blocks i,
+// i + NT, ..., then the block combines the threads as a tree over i, i + NT /
+// 2, ..., i + 64, ..., i + 1, so the order depends on G only (and with SPAN = 2
+// NT it is that of a block of 2 NT threads, of which one holds two). Up to 2048 / NT
+// columns go through the tree together: a few exchanges through LDS, then the
+// fold of the first wave, where one column at a time took eight barriers each
+// (the Lanczos H.x over 924 rows of 8 FP64 columns: 17.6 -> 11.8 us). tot[c]
+// (LDS, grid_sum_slots<VB, NT>() doubles) receives the totals, visible to the
+// first wave; red holds grid_sum_lds<VB, NT>() bytes of LDS.
+template <int VB, int NT = kBlock, int SPAN = NT>
 __device__ __forceinline__ void grid_sum_cols(const double* partials, int G, int pstride, int col0, int nc,
                                               double* red, double* tot) {
-    constexpr int W = grid_sum_group<VB>();
+    constexpr int W = grid_sum_group<VB, NT>();
     const int tid = int(threadIdx.x);
 #pragma unroll 1
     for (int c0 = 0; c0 < nc; c0 += W) {
@@ -214,14 +217,29 @@ __device__ __forceinline__ void grid_sum_cols(const double* partials, int G, int
 #pragma unroll
         for (int c = 0; c < W; ++c) s[c] = 0.0;
         const double* p = partials + col0 + c0;
-        for (int g = tid; g < G; g += kBlock) {
+#pragma unroll 4
+        for (int g = tid; g < G; g += SPAN) {
 #pragma unroll
             for (int c = 0; c < W; ++c)
                 if (c0 + c < nc) s[c] += *gptr(p + size_t(g) * pstride + c);
         }
+        if constexpr (SPAN > NT) {
+            static_assert(SPAN == 2 * NT, "one or two threads of the order in each");
+            double t[W];
+#pragma unroll
+            for (int c = 0; c < W; ++c) t[c] = 0.0;
+#pragma unroll 4
+            for (int g = tid + NT; g < G; g += SPAN) {
+#pragma unroll
+                for (int c = 0; c < W; ++c)
+                    if (c0 + c < nc) t[c] += *gptr(p + size_t(g) * pstride + c);
+            }
+#pragma unroll
+            for (int c = 0; c < W; ++c) s[c] += t[c];
+        }
         // threads without a partial hold zeros: with 64 blocks or fewer the
         // first wave holds every partial
-        for (int half = 128; half >= 64; half >>= 1) {
+        for (int half = NT / 2; half >= 64; half >>= 1) {
             if (G <= half) continue;
             __syncthreads();
             if (tid >= half && tid < 2 * half) {

@@ -29,6 +29,14 @@ __device__ __forceinline__ double lane_val(double v, int lane) {
     return __builtin_bit_cast(double, lo | (hi << 32));
 }
 
+// The same value, as the compiler cannot know: what is computed from it stays
+// where it is used. (Hoisted out of the loop over the items, the lane's part of
+// find() and load() held 80 registers through the bond loops.)
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Inclusive prefix sum over the lanes of a wave (every lane active).
 __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
     int x = int(v);
@@ -54,6 +62,7 @@ struct Run {
     uint32_t X, Y, Z;  // lane i: the terms of site N - 1 - i in the partners' first rows
 
     __device__ __forceinline__ void find(uint32_t row, const SectorDev& S, Binom C, int low_bits, int lane) {
+        lane = opaque(lane);
         const int N = S.n_sites;
         uint32_t rem = row;
         int A = S.n_up;
@@ -116,6 +125,7 @@ struct RunBonds {
     template <typename L>
     __device__ __forceinline__ void load(const Run<L>& run, const BondTable& B, int first, int low_bits, int lane,
                                          const unsigned char* xb, uint32_t ldb, uint32_t last) {
+        lane = opaque(lane);
         const int b = first + lane, N = B.n_sites;
         const bool on = lane < kSetBonds && b < B.n_bonds;
         const uint32_t pack = on ? B.pack[b] : 0u;
@@ -185,133 +195,157 @@ struct RunSlot {
     T c[G];
 };
 
-// y = H x on the sector rows [pos, end) by one wave, 64 R rows of a run at a
-// time (lane l: rows l, l + 64, ...). y holds sector row `row0` at its start;
-// `low` is the rank table in LDS. Bonds go in the sorted order of the bond
-// table, G at a time into two slots in turn: a slot's rows are added to the
-// sums after the other slot's loads are issued. Those between high sites come
-// first and only where they flip; a row whose bond does not flip loads
-// nothing (an offset past the buffer gives 0). Every sum has the terms of the
-// row-by-row kernel in the same order.
-template <typename L, typename T, int VB, int R, int G>
-__device__ __forceinline__ void run_rows(const SectorDev& S, const BondTable& B, const unsigned char* low, Binom C,
-                                         int low_bits, const T* __restrict__ x, T* __restrict__ y, uint64_t ld,
-                                         uint32_t col0, uint32_t row0, uint32_t pos, uint32_t end) {
+// The rows lo <= t < hi of one run among the 64 R rows that begin at row p0
+// (lane l: rows p0 + l, p0 + 64 + l, ...): y = H x, or the Lanczos epilogue w =
+// hv_a (H u_k) - hv_b u_{k-1} of hv_body, whose products u_k[t] w[t] go to
+// prod (zero for the block's other rows). y holds sector row
+// `row0` at its start; `low` is the rank table in LDS. Bonds go in the sorted
+// order of the bond table, G at a time into two slots in turn: a slot's rows
+// are added to the sums after the other slot's loads are issued. Those between
+// high sites come first and only where they flip; a row whose bond does not
+// flip loads nothing (an offset past the buffer gives 0). Every sum has the
+// terms of the row-by-row kernel in the same order.
+template <typename L, typename T, int VB, int R, int G, int EPI>
+__device__ __forceinline__ void run_block(const SectorDev& S, const BondTable& B, const unsigned char* low,
+                                          int low_bits, const Run<L>& run, RunBonds<T>& rb,
+                                          const T* __restrict__ x, T* __restrict__ y, uint64_t ld, uint32_t col0,
+                                          uint32_t row0, uint32_t p0, uint32_t lo, uint32_t hi, const T* ab,
+                                          bool first, double (&prod)[R][VB]) {
     const int lane = threadIdx.x & 63;
     const uint32_t ldb = uint32_t(ld * sizeof(T));
     const unsigned char* xb = reinterpret_cast<const unsigned char*>(x + col0);
     const int n_bonds = __builtin_amdgcn_readfirstlane(B.n_bonds);
     const int n_high = __builtin_amdgcn_readfirstlane(int(B.ends[low_bits]));
     const T jsum4 = sizeof(T) == 4 ? T(B.jsum4_f) : T(B.jsum4_d);
+    const uint16_t* pat = kLow.pattern + kLow.first[run.k];
+    // rows by their position in the run (p0 may lie before it)
+    const uint32_t j0 = p0 - run.base, jlo = lo - run.base, jn = hi - lo;
+    uint32_t voff[R], l2[R];
+    T acc[R][VB], anti[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const uint32_t j = j0 + uint32_t(64 * i + lane);
+        const bool in = j - jlo < jn;
+        voff[i] = in ? __umul24(j, ldb) : kNoRow;
+        l2[i] = 2u * uint32_t(*gptr(pat + (in ? j : jlo)));
+        anti[i] = T(0);
+#pragma unroll
+        for (int c = 0; c < VB; ++c) acc[i][c] = T(0);
+    }
+    T ah = T(0);
+    RunSlot<T, VB, R, G> sa, sb;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        sb.c[g] = T(0);
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int k = 0; k < VB; ++k) sb.v[g][i][k] = T(0);
+    }
+    auto add = [&](auto& sl) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int k = 0; k < VB; ++k) acc[i][k] += sl.c[g] * sl.v[g][i][k];
+    };
+#pragma unroll 1
+    for (int set = 0; set < n_bonds; set += kSetBonds) {
+        if (n_bonds > kSetBonds) rb.load(run, B, set, low_bits, lane, xb, ldb, S.dim - 1);
+        uint64_t fl = rb.flips;
+        auto high = [&](auto& sl) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int b = __builtin_ctzll(fl);
+                fl = (fl & (fl - 1)) | (uint64_t(1) << kSetBonds);
+                sl.c[g] = lane_val(rb.coef, b);
+                const auto rs = run_rsrc(lane_u32(rb.blo, b), lane_u32(rb.bhi, b), b < kSetBonds ? kNoRow : 0u);
+#pragma unroll
+                for (int i = 0; i < R; ++i) buffer_row<T, VB>(rs, voff[i], sl.v[g][i]);
+                ah += sl.c[g];
+            }
+        };
+        int b = n_high > set ? n_high - set : 0;
+        auto lows = [&](auto& sl) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int bb = b + g < kSetBonds ? b + g : kSetBonds;
+                const uint32_t pm = lane_u32(rb.mask, bb);
+                const uint32_t mask = pm & 0x3fffffffu, odd = pm >> 30;
+                sl.c[g] = lane_val(rb.coef, bb);
+                const auto rs = run_rsrc(lane_u32(rb.blo, bb), lane_u32(rb.bhi, bb), kNoRow);
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const uint32_t no = (uint32_t(__popc(l2[i] & mask)) + odd) << 31;  // kNoRow unless the row flips
+                    const uint32_t rank = *reinterpret_cast<const uint16_t*>(low + (l2[i] ^ mask));
+                    buffer_row<T, VB>(rs, __umul24(rank, ldb) + no, sl.v[g][i]);
+                    anti[i] += no ? T(0) : sl.c[g];
+                }
+            }
+            b += G;
+        };
+        while (fl != uint64_t(1) << kSetBonds) {
+            high(sa);
+            add(sb);
+            high(sb);
+            add(sa);
+        }
+        if (set == 0 || n_high > set) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) anti[i] = ah;
+        }
+        const int nb = n_bonds - set < kSetBonds ? n_bonds - set : kSetBonds;
+        while (b < nb) {
+            lows(sa);
+            add(sb);
+            lows(sb);
+            add(sa);
+        }
+    }
+    add(sb);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const uint32_t j = j0 + uint32_t(64 * i + lane);
+        if constexpr (EPI == kEpiLanczos) {
+#pragma unroll
+            for (int c = 0; c < VB; ++c) prod[i][c] = 0.0;
+        }
+        if (j - jlo < jn) {
+            const uint32_t t = run.base + j;
+            T xt[VB], out[VB];
+            load_row<T, VB>(reinterpret_cast<const T*>(xb + uint64_t(t) * ldb), xt);
+            const T diag = jsum4 - anti[i];
+#pragma unroll
+            for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[i][c];
+            T* yrow = y + uint64_t(t - row0) * ld + col0;
+            if constexpr (EPI == kEpiLanczos) {
+                lanczos_epilogue<T, VB>(xt, out, yrow, ab, first, prod[i]);
+            }
+            store_row<T, VB>(yrow, out);
+        }
+    }
+}
+
+// y = H x on the sector rows [pos, end) by one wave, 64 R rows of a run at a
+// time.
+template <typename L, typename T, int VB, int R, int G>
+__device__ __forceinline__ void run_rows(const SectorDev& S, const BondTable& B, const unsigned char* low, Binom C,
+                                         int low_bits, const T* __restrict__ x, T* __restrict__ y, uint64_t ld,
+                                         uint32_t col0, uint32_t row0, uint32_t pos, uint32_t end) {
+    const int lane = threadIdx.x & 63;
+    double none[R][VB];
     while (pos < end) {
         Run<L> run;
         run.find(pos, S, C, low_bits, lane);
-        const uint32_t lim = end < run.base + run.size ? end : run.base + run.size;
-        const uint16_t* pat = kLow.pattern + kLow.first[run.k];
+        const uint32_t lim = end - run.base < run.size ? end : run.base + run.size;
         RunBonds<T> rb;
-        rb.load(run, B, 0, low_bits, lane, xb, ldb, S.dim - 1);
-        const uint32_t stop = lim - run.base;  // rows by their position in the run from here on
+        rb.load(run, B, 0, low_bits, lane, reinterpret_cast<const unsigned char*>(x + col0), uint32_t(ld * sizeof(T)),
+                S.dim - 1);
 #pragma unroll 1
-        for (uint32_t p = pos - run.base; p < stop; p += uint32_t(64 * R)) {
-            uint32_t voff[R], l2[R];
-            T acc[R][VB], anti[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const uint32_t j = p + uint32_t(64 * i + lane);
-                voff[i] = j < stop ? __umul24(j, ldb) : kNoRow;
-                l2[i] = 2u * uint32_t(*gptr(pat + (j < stop ? j : p)));
-                anti[i] = T(0);
-#pragma unroll
-                for (int c = 0; c < VB; ++c) acc[i][c] = T(0);
-            }
-            T ah = T(0);
-            RunSlot<T, VB, R, G> sa, sb;
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                sb.c[g] = T(0);
-#pragma unroll
-                for (int i = 0; i < R; ++i)
-#pragma unroll
-                    for (int k = 0; k < VB; ++k) sb.v[g][i][k] = T(0);
-            }
-            auto add = [&](auto& sl) {
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int i = 0; i < R; ++i)
-#pragma unroll
-                        for (int k = 0; k < VB; ++k) acc[i][k] += sl.c[g] * sl.v[g][i][k];
-            };
-#pragma unroll 1
-            for (int set = 0; set < n_bonds; set += kSetBonds) {
-                if (n_bonds > kSetBonds) rb.load(run, B, set, low_bits, lane, xb, ldb, S.dim - 1);
-                uint64_t fl = rb.flips;
-                auto high = [&](auto& sl) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const int b = __builtin_ctzll(fl);
-                        fl = (fl & (fl - 1)) | (uint64_t(1) << kSetBonds);
-                        sl.c[g] = lane_val(rb.coef, b);
-                        const auto rs = run_rsrc(lane_u32(rb.blo, b), lane_u32(rb.bhi, b), b < kSetBonds ? kNoRow : 0u);
-#pragma unroll
-                        for (int i = 0; i < R; ++i) buffer_row<T, VB>(rs, voff[i], sl.v[g][i]);
-                        ah += sl.c[g];
-                    }
-                };
-                int b = n_high > set ? n_high - set : 0;
-                auto lows = [&](auto& sl) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const int bb = b + g < kSetBonds ? b + g : kSetBonds;
-                        const uint32_t pm = lane_u32(rb.mask, bb);
-                        const uint32_t mask = pm & 0x3fffffffu, odd = pm >> 30;
-                        sl.c[g] = lane_val(rb.coef, bb);
-                        const auto rs = run_rsrc(lane_u32(rb.blo, bb), lane_u32(rb.bhi, bb), kNoRow);
-#pragma unroll
-                        for (int i = 0; i < R; ++i) {
-                            const uint32_t no = (uint32_t(__popc(l2[i] & mask)) + odd) << 31;  // kNoRow unless the row flips
-                            const uint32_t lo = *reinterpret_cast<const uint16_t*>(low + (l2[i] ^ mask));
-                            buffer_row<T, VB>(rs, __umul24(lo, ldb) + no, sl.v[g][i]);
-                            anti[i] += no ? T(0) : sl.c[g];
-                        }
-                    }
-                    b += G;
-                };
-                while (fl != uint64_t(1) << kSetBonds) {
-                    high(sa);
-                    add(sb);
-                    high(sb);
-                    add(sa);
-                }
-                if (set == 0 || n_high > set) {
-#pragma unroll
-                    for (int i = 0; i < R; ++i) anti[i] = ah;
-                }
-                const int nb = n_bonds - set < kSetBonds ? n_bonds - set : kSetBonds;
-                while (b < nb) {
-                    lows(sa);
-                    add(sb);
-                    lows(sb);
-                    add(sa);
-                }
-            }
-            add(sb);
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const uint32_t j = p + uint32_t(64 * i + lane);
-                if (j < stop) {
-                    const uint32_t t = run.base + j;
-                    T xt[VB], out[VB];
-                    load_row<T, VB>(reinterpret_cast<const T*>(xb + uint64_t(t) * ldb), xt);
-                    const T diag = jsum4 - anti[i];
-#pragma unroll
-                    for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[i][c];
-                    T* yrow = y + uint64_t(t - row0) * ld + col0;
-                    store_row<T, VB>(yrow, out);
-                }
-            }
-        }
-        pos = lim;
+        for (; pos < lim; pos = lim - pos > uint32_t(64 * R) ? pos + uint32_t(64 * R) : lim)
+            run_block<L, T, VB, R, G, kEpiPlain>(S, B, low, low_bits, run, rb, x, y, ld, col0, row0, pos, pos, lim,
+                                                 nullptr, false, none);
     }
 }
 

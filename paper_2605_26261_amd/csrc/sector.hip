@@ -4,12 +4,9 @@
 
 namespace ftlm {
 
-template <typename T>
-hipError_t launch_hv_typed(const SectorDev&, const BondTable&, const HvLaunch&, hipStream_t);
-
 hipError_t launch_hv(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
     if (s.two_s > 1) return launch_hv_spin(s, B, h, st);
-    return h.dtype == 0 ? launch_hv_typed<float>(s, B, h, st) : launch_hv_typed<double>(s, B, h, st);
+    return h.dtype == 0 ? launch_hv_f32(s, B, h, st) : launch_hv_f64(s, B, h, st);
 }
 
 namespace {

@@ -5,6 +5,7 @@
 // keep their own kernels (hv_impl.hpp, sector.hip).
 #include "hv_impl.hpp"
 #include "spin.hpp"
+#include "spinruns.hpp"
 
 namespace ftlm {
 
@@ -190,11 +191,11 @@ constexpr int spin_slot_bonds(int vb, int epi) { return (vb == 8 && epi == kEpiL
 template <int MODE, typename T, int VB, int EPI>
 __device__ __forceinline__ void hv_spin_body(const SectorDev& S, const BondTable& B, const SpinLds& l,
                                              const T* __restrict__ x, T* __restrict__ y, uint64_t ld, uint32_t col0,
-                                             uint32_t row0, uint32_t nrows, uint32_t bid, uint32_t G, const T* ab,
-                                             bool first, double* wsum) {
+                                             uint32_t row0, uint32_t nrows, uint32_t bid, uint32_t G, int shift,
+                                             const T* ab, bool first, double* wsum) {
     const int wave = threadIdx.x >> 6;
     const uint32_t ntiles = (nrows + kBlock - 1) / kBlock;
-    for_each_tile(ntiles, bid, G, kXcdSuperShift, [&](uint32_t tile) {
+    for_each_tile(ntiles, bid, G, shift, [&](uint32_t tile) {
         const uint32_t r = tile * kBlock + threadIdx.x;
         const bool valid = r < nrows;
         T xt[VB], out[VB];
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(kBlock) void hv_spin_kernel(SectorDev S, BondTable 
     const SpinLds l = spin_lds_setup<MODE>(smem, S);
     __syncthreads();
     hv_spin_body<MODE, T, VB, kEpiPlain>(S, Bs, l, static_cast<const T*>(h.x), static_cast<T*>(h.y), h.ld, h.col0,
-                                         h.row0, h.nrows, blockIdx.x, gridDim.x, nullptr, false, nullptr);
+                                         h.row0, h.nrows, blockIdx.x, gridDim.x, h.super_shift, nullptr, false, nullptr);
 }
 
 // First half of a Lanczos step over the sectors of the launch, as
@@ -277,8 +278,8 @@ __global__ __launch_bounds__(kBlock) void hv_spin_lanczos_kernel(LanczosLaunch a
         __syncthreads();
         const T* x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
         T* y = uniform(static_cast<T*>(sw.u[step & 1]));
-        hv_spin_body<MODE, T, VB, kEpiLanczos>(S, B, l, x, y, a.ld, a.col0, 0, S.dim, local, uniform(sw.items), ab,
-                                               step == 1, wsum);
+        hv_spin_body<MODE, T, VB, kEpiLanczos>(S, B, l, x, y, a.ld, a.col0, 0, S.dim, local, uniform(sw.items),
+                                               kXcdSuperShift, ab, step == 1, wsum);
         store_partials<VB>(sw, a, wsum, local);
         __syncthreads();  // LDS (bonds, scalars, tables) is restaged by the next item
     }
@@ -287,6 +288,52 @@ __global__ __launch_bounds__(kBlock) void hv_spin_lanczos_kernel(LanczosLaunch a
         for (int s = 0; s < a.nsec; ++s)
             if (uniform(secs[s].state[1]) != 0) finish_alpha<VB>(secs[s], a, secs[s].items, red);
     }
+}
+
+// ---- by runs -----------------------------------------------------------------
+
+template <typename T>
+__device__ __forceinline__ HighDim stage_spin_runs(unsigned char* smem, const SectorDev& S, const SpinLow& L,
+                                                   PairTable<T>& pairs) {
+    // two ranks a word (after an odd count the table has two bytes of padding)
+    uint32_t* rank = reinterpret_cast<uint32_t*>(smem);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(L.rank);
+    const int words = int(spin_low_strings(L.d) + 1) / 2;
+    for (int i = threadIdx.x; i < words; i += blockDim.x) rank[i] = *gptr(src + i);
+    uint32_t* dims = reinterpret_cast<uint32_t*>(smem + spin_runs_rank_bytes(S));
+    const int per = S.bw * L.d, count = (S.n_sites - L.sites) * per;
+    for (int i = threadIdx.x; i < count; i += blockDim.x) dims[i] = *gptr(S.binom + L.sites * per + i);
+    pairs.stage(S.two_s);
+    return HighDim{dims, S.bw, L.d, L.sites};
+}
+
+// The plain H.x by runs: every wave takes `chunk` consecutive rows at a time.
+//
+// What bounds it: s = 5/2, 144,840,476 rows, one FP32 vector 8.4 -> 4.3 ms. The
+// row-by-row kernel issues 2300 VALU instructions per 64 rows, half of them for
+// the walk down the digits; by runs about half of them are left and the partner
+// lines that miss L2 take as long (two columns 8.7 -> 5.6 ms, one FP64 9.6 -> 6.0).
+template <typename T, int VB>
+__global__ __launch_bounds__(kBlock) void hv_spin_runs_kernel(SectorDev S, BondTable B, HvLaunch h) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ BondTable Bs;
+    __shared__ __align__(16) PairTable<T> pairs;
+    stage_bonds(Bs, &B);
+    const SpinLow L = spin_low(S);
+    const HighDim D = stage_spin_runs(smem, S, L, pairs);
+    __syncthreads();
+    const uint32_t wave = uniform(threadIdx.x >> 6);
+    const uint32_t block_rows = kWaves * h.chunk;
+    const uint32_t ntiles = uint32_t((uint64_t(h.nrows) + block_rows - 1) / block_rows);
+    for_each_tile(ntiles, blockIdx.x, gridDim.x, h.super_shift, [&](uint32_t tile) {
+        const uint64_t r0 = uint64_t(tile) * block_rows + uint64_t(wave) * h.chunk;
+        if (r0 >= h.nrows) return;
+        const uint32_t n = h.nrows - uint32_t(r0) < h.chunk ? h.nrows - uint32_t(r0) : h.chunk;
+        const uint32_t pos = h.row0 + uint32_t(r0);
+        spin_run_rows<T, VB, 2>(
+            S, Bs, reinterpret_cast<const uint16_t*>(smem), D, L, pairs.v, static_cast<const T*>(h.x),
+            static_cast<T*>(h.y), h.ld, h.col0, h.row0, pos, pos + n);
+    });
 }
 
 template <typename F>
@@ -438,9 +485,60 @@ __global__ __launch_bounds__(kBlock) void neighbors_spin_kernel(SectorDev S, Bon
 
 }  // namespace
 
+// Whether a product goes by runs: rows of up to 8 bytes (wider ones are bound by
+// the lines they miss: s = 5/2, M = 0, four FP32 columns 10.4 ms row by row, 11.3
+// by runs), from 2^23 of them (s = 3/2, 1.7 million: 104 against 111 us), at least
+// 192 to a run on average. Icosahedron, FP32, one column: s = 2, M = 0 with 260 a
+// run 1100 -> 838 us, M = 6 with 130 564 against 764; s = 5/2, M = 8 with 220 3484
+// -> 2288, M = 12 with 85 1442 -> 1299 (with the compressed table 925).
+static bool spin_by_runs(const SectorDev& s, size_t row_bytes, uint64_t ldb) {
+    const int d = s.two_s + 1, low = spin_low_sites(d), nh = s.n_sites - low;
+    if (d > 6 || nh <= 0 || row_bytes > 8 || s.dim < (1u << 23)) return false;
+    if (ldb > (uint64_t(1) << 19)) return false;  // a run's rows lie within 2^31 bytes
+    // high patterns that leave the low sites a digit sum they can have
+    double count[kMaxSpinSites * kMaxTwoS + 1] = {1.0};
+    for (int q = 0; q < nh; ++q) {
+        double window = 0.0, old[kMaxTwoS + 1] = {};
+        for (int k = 0; k <= (q + 1) * s.two_s; ++k) {
+            const double c = k <= q * s.two_s ? count[k] : 0.0;
+            window += c - old[k % d];
+            old[k % d] = c;
+            count[k] = window;
+        }
+    }
+    double runs = 0.0;
+    for (int k = 0; k <= nh * s.two_s && k <= s.n_up; ++k)
+        if (s.n_up - k <= low * s.two_s) runs += count[k];
+    return double(s.dim) >= 192.0 * runs;
+}
+
+template <typename T, int VB>
+hipError_t launch_hv_spin_runs(const SectorDev& s, const BondTable& B, HvLaunch h, hipStream_t st) {
+    constexpr uint32_t kStep = 128, kChunk = 512;
+    uint32_t steps = h.nrows / (8192u * kStep);
+    steps = steps < 1 ? 1 : steps > kChunk / kStep ? kChunk / kStep : steps;
+    h.chunk = steps * kStep;
+    const uint64_t blocks = (uint64_t(h.nrows) + kWaves * h.chunk - 1) / (uint64_t(kWaves) * h.chunk);
+    const uint64_t most = VB * sizeof(T) <= 4 ? 8192 : uint64_t(1) << 30;
+    h.grid = int(blocks < 8 ? blocks : blocks < most ? (blocks + 7) & ~uint64_t(7) : most);
+    h.super_shift = plain_super_shift(blocks, 6);
+    const size_t lds = spin_runs_lds(s);
+    auto kern = hv_spin_runs_kernel<T, VB>;
+    hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(unsigned(h.grid)), dim3(kBlock), lds, st, s, B, h);
+    return hipGetLastError();
+}
+
 hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
     HvLaunch h = h0;
-    h.grid = int(rows_grid(h.nrows));
+    const size_t row_bytes = size_t(h.vb) * (h.dtype == 0 ? 4 : 8);
+    if (spin_by_runs(s, row_bytes, h.ld * (h.dtype == 0 ? 4 : 8))) {
+        if (h.dtype != 0) return launch_hv_spin_runs<double, 1>(s, B, h, st);
+        return h.vb == 1 ? launch_hv_spin_runs<float, 1>(s, B, h, st) : launch_hv_spin_runs<float, 2>(s, B, h, st);
+    }
+    h.grid = int(hv_grid(h.nrows, row_bytes));
+    h.super_shift = plain_super_shift((uint64_t(h.nrows) + kBlock - 1) / kBlock, row_bytes <= 16 ? 4 : 6);
     const size_t lds = hv_spin_lds_bytes(s);
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);
@@ -460,12 +558,12 @@ hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch
 }
 
 hipError_t launch_hv_lanczos_spin(const LanczosLaunch& a, size_t lds, hipStream_t st) {
+    if (!a.queue || a.items <= 0) return hipErrorInvalidValue;  // the queue counters are required
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);
         constexpr int MODE = decltype(mm)::value;
         return with_spin_vb(a.vb, [&](auto vb) {
             auto kern = hv_spin_lanczos_kernel<MODE, T, decltype(vb)::value>;
-            if (!a.queue || a.items <= 0) return hipErrorInvalidValue;  // the queue counters are required
             const size_t bytes = lds < kGridSumLds ? kGridSumLds : lds;  // the final sums reuse the block's LDS
             hipError_t e = allow_lds(kern, bytes);
             if (e != hipSuccess) return e;

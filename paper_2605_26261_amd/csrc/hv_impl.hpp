@@ -308,6 +308,29 @@ __device__ __forceinline__ void stage_epilogue(T* ab, const Chain* chains) {
     }
 }
 
+// Row t of a Lanczos step by one lane: w = hv_a (H u_k) - hv_b u_{k-1} and the
+// products u_k w. `ylds` is the lane's own [site] column of Y values (ranking).
+template <typename L, int MODE, typename T, int VB>
+__device__ __forceinline__ void walk_row(uint32_t t, const SectorDev& S, const BondTable& B, Binom C, uint32_t* ylds,
+                                         const T* __restrict__ x, T* __restrict__ y, uint64_t ld, uint32_t col0,
+                                         const T* ab, bool first, double (&prod)[VB]) {
+    T acc[VB], xt[VB], out[VB];
+#pragma unroll
+    for (int c = 0; c < VB; ++c) acc[c] = T(0);
+    T anti = T(0);
+    GatherVisitor<T, VB, site_group(VB, kEpiLanczos)> vis{
+        reinterpret_cast<const unsigned char*>(x + col0), uint32_t(ld * sizeof(T)), S.dim - 1,
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x), 0, 0, kBufferWord3), B, acc, anti};
+    visit_row<L, MODE>(t, S.n_up, B, C, S.basis, table_map<MODE>(S), ylds, vis);
+    load_row<T, VB>(x + uint64_t(t) * ld + col0, xt);
+    const T diag = (sizeof(T) == 4 ? T(B.jsum4_f) : T(B.jsum4_d)) - anti;
+#pragma unroll
+    for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];
+    T* yrow = y + uint64_t(t) * ld + col0;
+    lanczos_epilogue<T, VB>(xt, out, yrow, ab, first, prod);
+    store_row<T, VB>(yrow, out);
+}
+
 // The block's FP64 partials of <u_k, w> for its VB columns (wsum: one row of
 // VB per wave) into its slot of the sector's partials.
 template <int VB>
@@ -602,16 +625,6 @@ hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunc
         if constexpr (std::is_same_v<L, uint32_t> && (MODE == kModeCr || MODE == kModeClt))
             if (buf) return launch_hv_one<L, MODE, T, 1, true>(sm, B, h, st);
         return with_vb<T>(h.vb, [&](auto vb) { return launch_hv_one<L, MODE, T, decltype(vb)::value>(sm, B, h, st); });
-    });
-}
-
-template <typename T>
-hipError_t launch_lanczos_typed(int mode, int n_sites, const LanczosLaunch& a, size_t lds, hipStream_t st) {
-    return with_mode(mode, n_sites, [&](auto l, auto m) {
-        using L = decltype(l);
-        return with_vb<T>(a.vb, [&](auto vb) {
-            return launch_lanczos_one<L, decltype(m)::value, T, decltype(vb)::value>(a, lds, st);
-        });
     });
 }
 

@@ -4,6 +4,7 @@
 // the index kernels (rank, unrank, neighbour lists). The spin-1/2 sectors
 // keep their own kernels (hv_impl.hpp, sector.hip).
 #include "hv_impl.hpp"
+#include "lanczos_small.hpp"
 #include "spin.hpp"
 #include "spinruns.hpp"
 
@@ -336,6 +337,31 @@ __global__ __launch_bounds__(kBlock) void hv_spin_runs_kernel(SectorDev S, BondT
     });
 }
 
+// The Lanczos step's H.x of a small sector (small_lanczos_items).
+template <int MODE, typename T, int VB>
+__global__ __launch_bounds__(kSmallThreads) void hv_spin_small_lanczos_kernel(LanczosLaunch a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ BondTable B;
+    small_lanczos<T, VB>(a, B, smem, [&](const SectorDev& S, uint32_t col0) {
+        const SpinLds l = spin_lds_setup<MODE>(smem, S);
+        return [=](uint32_t t, const T* x, T* y, const T* ab, bool first, double (&prod)[VB]) {
+            T acc[VB], xt[VB], out[VB];
+#pragma unroll
+            for (int c = 0; c < VB; ++c) acc[c] = T(0);
+            T diag = T(0);
+            SpinGather<T, VB, spin_slot_bonds(VB, kEpiLanczos)> vis{
+                reinterpret_cast<const unsigned char*>(x + col0), uint32_t(a.ld * sizeof(T)), S.dim - 1, B, acc, diag};
+            spin_row<MODE, T>(t, S, B, l, vis);
+            load_row<T, VB>(x + uint64_t(t) * a.ld + col0, xt);
+#pragma unroll
+            for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];
+            T* yrow = y + uint64_t(t) * a.ld + col0;
+            lanczos_epilogue<T, VB>(xt, out, yrow, ab, first, prod);
+            store_row<T, VB>(yrow, out);
+        };
+    });
+}
+
 template <typename F>
 hipError_t with_spin_vb(int vb, F&& f) {
     switch (vb) {
@@ -559,6 +585,21 @@ hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch
 
 hipError_t launch_hv_lanczos_spin(const LanczosLaunch& a, size_t lds, hipStream_t st) {
     if (!a.queue || a.items <= 0) return hipErrorInvalidValue;  // the queue counters are required
+    const size_t small = small_lanczos_lds(lds, 2 * hv_slab_lds_bytes(a.n_sites, a.mode));
+    if (by_small_lanczos(a, small)) {
+        auto narrow = [&](auto tt, auto mm) {
+            using T = decltype(tt);
+            constexpr int MODE = decltype(mm)::value;
+            return with_small_vb(a, [&](auto vb) {
+                return launch_small_lanczos(hv_spin_small_lanczos_kernel<MODE, T, decltype(vb)::value>,
+                                            decltype(vb)::value, a, small, st);
+            });
+        };
+        const auto cr = std::integral_constant<int, kModeCr>{};
+        const auto clt = std::integral_constant<int, kModeClt>{};
+        if (a.dtype == 0) return a.mode == kModeCr ? narrow(float{}, cr) : narrow(float{}, clt);
+        return a.mode == kModeCr ? narrow(double{}, cr) : narrow(double{}, clt);
+    }
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);
         constexpr int MODE = decltype(mm)::value;

@@ -51,32 +51,6 @@ inline size_t lanczos_rows_lds(int path, int n_sites, int low_bits, int threads)
     return n < kGridSumLds ? kGridSumLds : n;
 }
 
-// The 64 rows t0 + lane below `end` by one wave, row by row: w = hv_a (H u_k) -
-// hv_b u_{k-1} and the rows' products u_k w.
-template <typename L, int MODE, typename T, int VB>
-__device__ __forceinline__ void walk_block(const SectorDev& S, const BondTable& B, Binom C, uint32_t* ylds,
-                                           const T* __restrict__ x, T* __restrict__ y, uint64_t ld, uint32_t col0,
-                                           uint32_t t0, uint32_t end, const T* ab, bool first, double (&prod)[VB]) {
-    const uint32_t lane = threadIdx.x & 63u;
-    if (lane >= end - t0) return;
-    const uint32_t t = t0 + lane;
-    T acc[VB], xt[VB], out[VB];
-#pragma unroll
-    for (int c = 0; c < VB; ++c) acc[c] = T(0);
-    T anti = T(0);
-    GatherVisitor<T, VB, site_group(VB, kEpiLanczos)> vis{
-        reinterpret_cast<const unsigned char*>(x + col0), uint32_t(ld * sizeof(T)), S.dim - 1,
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x), 0, 0, kBufferWord3), B, acc, anti};
-    visit_row<L, MODE>(t, S.n_up, B, C, S.basis, table_map<MODE>(S), ylds, vis);
-    load_row<T, VB>(x + uint64_t(t) * ld + col0, xt);
-    const T diag = (sizeof(T) == 4 ? T(B.jsum4_f) : T(B.jsum4_d)) - anti;
-#pragma unroll
-    for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];
-    T* yrow = y + uint64_t(t) * ld + col0;
-    lanczos_epilogue<T, VB>(xt, out, yrow, ab, first, prod);
-    store_row<T, VB>(yrow, out);
-}
-
 // One Lanczos step's H.x over every sector of the launch (one sector, all
 // sectors of a plan, or a server round): w = H q_k - beta_{k-1} q_{k-1} and
 // the FP64 partials of <u_k, w>, summed in slot order into alpha_k (and the
@@ -214,7 +188,9 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
                         double prod[VB];
 #pragma unroll
                         for (int c = 0; c < VB; ++c) prod[c] = 0.0;
-                        walk_block<L, PATH, T, VB>(S, B, C, ylds, x, y, a.ld, a.col0, p0, stop, ab, first, prod);
+                        if (p0 + uint32_t(lane) < stop)
+                            walk_row<L, PATH, T, VB>(p0 + uint32_t(lane), S, B, C, ylds, x, y, a.ld, a.col0, ab, first,
+                                                     prod);
                         wave_fold_columns<VB, false>(prod, sums);
                         sums += VB;
                         if (stop == end) break;

@@ -200,7 +200,8 @@ __host__ __device__ constexpr int grid_sum_slots() {
 // nc - 1 (nc <= VB), partials[g * pstride + col]: thread i of NT sums blocks i,
 // i + NT, ..., then the block combines the threads as a tree over i, i + NT /
 // 2, ..., i + 64, ..., i + 1, so the order depends on G only (and with SPAN = 2
-// NT it is that of a block of 2 NT threads, of which one holds two). Up to 2048 / NT
+// NT it is that of a block of 2 NT threads, of which one holds two; the threads past
+// NT of a larger block only pass the barriers). Up to 2048 / NT
 // columns go through the tree together: a few exchanges through LDS, then the
 // fold of the first wave, where one column at a time took eight barriers each
 // (the Lanczos H.x over 924 rows of 8 FP64 columns: 17.6 -> 11.8 us). tot[c]
@@ -218,7 +219,7 @@ __device__ __forceinline__ void grid_sum_cols(const double* partials, int G, int
         for (int c = 0; c < W; ++c) s[c] = 0.0;
         const double* p = partials + col0 + c0;
 #pragma unroll 4
-        for (int g = tid; g < G; g += SPAN) {
+        for (int g = tid < NT ? tid : G; g < G; g += SPAN) {
 #pragma unroll
             for (int c = 0; c < W; ++c)
                 if (c0 + c < nc) s[c] += *gptr(p + size_t(g) * pstride + c);

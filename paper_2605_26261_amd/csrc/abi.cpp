@@ -426,7 +426,8 @@ int ftlm_start_vectors(const ftlm_sector* s, uint64_t seed, uint64_t r0, int R, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     LanczosJob job;
     single_job(job, s, nullptr, R, 1, dtype, work_dev);
-    job.secs[0].u[0] = q_dev;  // the start block goes to the caller's buffer
+    job.secs[0].u[0] = q_dev;  // the start block goes to the caller's buffer, all columns of a row together
+    job.chunks = {{0, R}};
     if (int rc = job_start(job, seed, r0, dist, st)) return rc;
     std::vector<Chain> ch(static_cast<size_t>(R));
     HIP_CHECK(hipMemcpyAsync(ch.data(), job.secs[0].chains, size_t(R) * sizeof(Chain), hipMemcpyDeviceToHost, st));
@@ -561,7 +562,8 @@ int ftlm_autotune(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype, v
     };
     auto batch_ms = [&](int x) {
         double t = 0.0;
-        for (auto [col, w] : column_chunks_v(x, uint64_t(x), dtype, {}, widest)) t += measured(w);
+        for (auto [col, w] : column_chunks_v(x, 0, dtype, {}, lanczos_width(s->two_s, s->n_sites, dtype)))
+            t += measured(w);
         return t;
     };
     // R chains in batches of b: R / b full batches and one of R mod b

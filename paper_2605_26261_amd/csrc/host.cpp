@@ -58,7 +58,7 @@ Stats g_stats;
 // ---- column chunking of a [D][ld] block --------------------------------------
 // Splits columns [0, nvec) into kernel widths of at most max_width, widest
 // first, keeping every vector access naturally aligned (ld, col0 and the base
-// pointers).
+// pointers; ld = 0 for columns kept launch by launch, see block_of).
 std::vector<std::pair<int, int>> column_chunks_v(int nvec, uint64_t ld, int dtype, const std::vector<const void*>& ptrs,
                                                  int max_width) {
     const size_t es = dtype == FTLM_F32 ? 4 : 8;
@@ -97,7 +97,7 @@ std::vector<std::pair<int, int>> job_chunks(const LanczosJob& job, int max_width
         ptrs.push_back(w.u[0]);
         ptrs.push_back(w.u[1]);
     }
-    return column_chunks_v(job.R, uint64_t(job.R), job.dtype, ptrs, max_width);
+    return column_chunks_v(job.R, 0, job.dtype, ptrs, max_width);
 }
 
 int check_dtype(int dtype) {
@@ -185,7 +185,7 @@ void job_layout(LanczosJob& job, const std::vector<SectorDev>& devs, const std::
     job.grid = int(block);
     job.items = int(items);
     job.lds = lds;
-    job.chunks = job_chunks(job, max_launch_width(job.two_s));
+    job.chunks = job_chunks(job, lanczos_width(job.two_s, job.n_sites, dtype));
 }
 
 // Start vectors of samples r0 .. r0 + R - 1 in every sector of the job.
@@ -206,10 +206,14 @@ int job_start(LanczosJob& job, uint64_t seed, uint64_t r0, int dist, hipStream_t
     LanczosLaunch a = job.launch();
     a.dist = dist;
     HIP_CHECK(launch_chain_init(a, st));
-    for (int c = 0; c < job.R; c += 4) {
-        a.col0 = uint32_t(c);
-        a.vb = std::min(4, job.R - c);
-        HIP_CHECK(launch_start(a, st));
+    for (auto [col, width] : job.chunks) {
+        a.block0 = uint32_t(col);
+        a.block_ld = uint32_t(width);
+        for (int c = 0; c < width; c += 4) {
+            a.col0 = uint32_t(col + c);
+            a.vb = std::min(4, width - c);
+            HIP_CHECK(launch_start(a, st));
+        }
     }
     return FTLM_OK;
 }
@@ -224,6 +228,8 @@ int job_steps(const LanczosJob& job, hipStream_t st, bool timed, int nsteps) {
         for (size_t i = 0; i < job.chunks.size(); ++i) {
             a.col0 = uint32_t(job.chunks[i].first);
             a.vb = job.chunks[i].second;
+            a.block0 = a.col0;
+            a.block_ld = uint32_t(a.vb);
             a.last_chunk = i + 1 == job.chunks.size() ? 1 : 0;
             if (timed) {
                 HvTimer timer(st);

@@ -117,6 +117,20 @@ std::vector<std::pair<int, int>> column_chunks(int nvec, uint64_t ld, int dtype,
                                                int max_width = 32);
 // Widest launch of the H.x kernels of a sector: 8 columns for general spin.
 inline int max_launch_width(int two_s) { return two_s > 1 ? 8 : 32; }
+// Columns of a Lanczos launch at most. Large sectors are bound by the partner
+// lines that miss L2, of which eight columns move the fewest per column (by runs
+// from 16 million rows); small ones by the launches. The line goes by the sites
+// alone, so that requests of one size run together whatever their sectors. 32
+// FP32 columns, a step, half filling, at most 32 / 20 or 16 / 8 columns a launch:
+// 18 sites 55 / 76 / 111 us, 20 sites 133 / 130 / 163, 21 sites 236 / 208 / 239, 22
+// sites 394 / 357 / 365, 24 sites 1385 / 1212 / 1116, 26 sites 6321 / 5368 / 4973; 20
+// columns at 21 sites 119 in one launch, 148 as 16 and 4. 16 FP64 columns, 16 / 8:
+// 18 sites 65 / 78, 20 sites 177 / 148, 24 sites 1362 / 1156.
+inline int lanczos_width(int two_s, int n_sites, int dtype) {
+    if (two_s > 1) return max_launch_width(two_s);
+    if (dtype != FTLM_F32) return n_sites <= 18 ? 16 : 8;
+    return n_sites <= 20 ? 32 : n_sites <= 22 ? 20 : 8;
+}
 int check_dtype(int dtype);
 
 // Byte offsets of one sector's Lanczos state inside a workspace or arena.

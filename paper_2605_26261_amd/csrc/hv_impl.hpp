@@ -397,9 +397,9 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
         double* wsum = lds.red;
         for (int i = threadIdx.x; i < kWaves * VB; i += kBlock) wsum[i] = 0.0;
         __syncthreads();
-        const T* x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
-        T* y = uniform(static_cast<T*>(sw.u[step & 1]));
-        hv_body<L, MODE, T, VB, kEpiLanczos>(S, B, lds, x, y, a.ld, a.col0, 0, S.dim, local, uniform(sw.items),
+        const T* x = uniform(block_of<T>(a, sw.u[(step - 1) & 1], S.dim));
+        T* y = uniform(block_of<T>(a, sw.u[step & 1], S.dim));
+        hv_body<L, MODE, T, VB, kEpiLanczos>(S, B, lds, x, y, a.block_ld, a.col0 - a.block0, 0, S.dim, local, uniform(sw.items),
                                              kXcdSuperShift, ab, step == 1, wsum);
         store_partials<VB>(sw, a, wsum, local);
         __syncthreads();  // LDS (bonds, scalars, tables) is restaged by the next item

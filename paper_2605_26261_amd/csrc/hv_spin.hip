@@ -277,9 +277,9 @@ __global__ __launch_bounds__(kBlock) void hv_spin_lanczos_kernel(LanczosLaunch a
         double* wsum = l.red;
         for (int i = threadIdx.x; i < kWaves * VB; i += kBlock) wsum[i] = 0.0;
         __syncthreads();
-        const T* x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
-        T* y = uniform(static_cast<T*>(sw.u[step & 1]));
-        hv_spin_body<MODE, T, VB, kEpiLanczos>(S, B, l, x, y, a.ld, a.col0, 0, S.dim, local, uniform(sw.items),
+        const T* x = uniform(block_of<T>(a, sw.u[(step - 1) & 1], S.dim));
+        T* y = uniform(block_of<T>(a, sw.u[step & 1], S.dim));
+        hv_spin_body<MODE, T, VB, kEpiLanczos>(S, B, l, x, y, a.block_ld, a.col0 - a.block0, 0, S.dim, local, uniform(sw.items),
                                                kXcdSuperShift, ab, step == 1, wsum);
         store_partials<VB>(sw, a, wsum, local);
         __syncthreads();  // LDS (bonds, scalars, tables) is restaged by the next item
@@ -350,12 +350,12 @@ __global__ __launch_bounds__(kSmallThreads) void hv_spin_small_lanczos_kernel(La
             for (int c = 0; c < VB; ++c) acc[c] = T(0);
             T diag = T(0);
             SpinGather<T, VB, spin_slot_bonds(VB, kEpiLanczos)> vis{
-                reinterpret_cast<const unsigned char*>(x + col0), uint32_t(a.ld * sizeof(T)), S.dim - 1, B, acc, diag};
+                reinterpret_cast<const unsigned char*>(x + col0), uint32_t(a.block_ld * sizeof(T)), S.dim - 1, B, acc, diag};
             spin_row<MODE, T>(t, S, B, l, vis);
-            load_row<T, VB>(x + uint64_t(t) * a.ld + col0, xt);
+            load_row<T, VB>(x + uint64_t(t) * a.block_ld + col0, xt);
 #pragma unroll
             for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];
-            T* yrow = y + uint64_t(t) * a.ld + col0;
+            T* yrow = y + uint64_t(t) * a.block_ld + col0;
             lanczos_epilogue<T, VB>(xt, out, yrow, ab, first, prod);
             store_row<T, VB>(yrow, out);
         };

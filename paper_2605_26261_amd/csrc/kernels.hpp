@@ -130,9 +130,11 @@ struct LanczosLaunch {
     int grid;            // total blocks (sum of the sectors' G, 8-aligned)
     int items;           // work items of the persistent H.x (sum of the sectors' items)
     uint64_t max_dim;    // the largest sector dimension (host launch tuning)
-    uint64_t ld;
-    uint32_t col0;
+    uint64_t ld;         // columns of the run: row stride of the partials
+    uint32_t col0;       // the launch's columns
     int vb;
+    uint32_t block0;     // the first column of the vector block that holds them, and
+    uint32_t block_ld;   // the block's columns: its row stride (block_of)
     int dtype;
     int last_chunk;      // this launch holds the last columns of a step
     double eps;          // stopping threshold
@@ -150,6 +152,15 @@ struct LanczosLaunch {
     // between launches), or null for a grid of one block per work item.
     uint32_t* queue;
 };
+
+// The columns of a run's vectors are kept launch by launch: those of a launch of
+// w columns form a [D][w] block of their own, after the blocks of the columns
+// before. A launch's gathers then read whole rows of what it works on. In one
+// [D][R] array, a launch of 8 of 32 columns fetched 128-byte lines for 32 bytes.
+template <typename T>
+__host__ __device__ inline T* block_of(const LanczosLaunch& a, void* u, uint32_t dim) {
+    return static_cast<T*>(u) + uint64_t(a.block0) * dim;
+}
 
 // The persistent Lanczos H.x takes its work items from eight counters, one
 // per XCD, and counts its exiting blocks in a ninth; the last block to exit

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
     if (s < 0) return;
     const SecWork& sw = a.secs[s];
     const uint32_t dim = sw.S.dim;
-    T* q = static_cast<T*>(sw.u[0]);
+    T* q = block_of<T>(a, sw.u[0], dim);
     const int nc = a.vb < CB ? a.vb : CB;
     double part[CB];
 #pragma unroll
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
             if (c < nc) {
                 const uint32_t col = a.col0 + c;
                 const T v = T(start_entry(a.dist, sw.keys[col], i, sw.r0 + col));
-                q[uint64_t(t) * a.ld + col] = v;
+                q[uint64_t(t) * a.block_ld + (col - a.block0)] = v;
                 part[c] += double(v) * double(v);
             }
         }
@@ -136,8 +136,8 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
 // stopping rule: a chain stops after step k when k reaches min(M, D) or
 // beta_k <= eps * max_{j<=k}(|alpha_j|, beta_{j-1}). A stopped chain gets
 // zero scales, so its columns stay zero in every later step.
-// Blocks whose rows are 32 to 128 bytes (a multiple of 8) go through LDS: the
-// rows of u and w staged together are contiguous, so they move with fully
+// Rows of 32 to 128 bytes (a multiple of 8) go through LDS: a tile's rows of u
+// and w are contiguous, so they move with fully
 // coalesced 16-byte accesses (8-byte ones for rows that are not a multiple of
 // 16 bytes), while each thread still updates its own row (the same arithmetic
 // and summation order as without the staging). With one thread per row, a
@@ -178,8 +178,8 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
     if (sw.state[1] == 0) return;
     const int step = sw.state[0];
     const uint32_t dim = sw.S.dim;
-    const T* __restrict__ u = static_cast<const T*>(sw.u[(step - 1) & 1]);
-    T* __restrict__ w = static_cast<T*>(sw.u[step & 1]);
+    const T* __restrict__ u = block_of<T>(a, sw.u[(step - 1) & 1], dim);
+    T* __restrict__ w = block_of<T>(a, sw.u[step & 1], dim);
     // the update coefficients, read once (through a generic pointer the
     // compiler would re-read them after every store of the tile loop)
     T coef[VB];
@@ -192,98 +192,92 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
 #pragma unroll
     for (int c = 0; c < VB; ++c) part[c] = 0.0;
     const uint32_t ntiles = (dim + kBlock - 1) / kBlock;
-    // whole rows of [D][ld] blocks: a tile is one contiguous range
-    const bool staged = kStage && a.col0 == 0 && a.ld == uint64_t(VB);
     if constexpr (kStage) {
-        if (staged) {
-            // copy unit: 16 bytes, or 8 for rows of an odd number of 8-byte words
-            constexpr int kUnit = (VB * sizeof(T)) % 16 == 0 ? 4 : 2;
-            using VU = uint32_t __attribute__((ext_vector_type(kUnit)));
-            constexpr uint32_t kRowUnits = uint32_t(VB * sizeof(T)) / uint32_t(4 * kUnit);
-            constexpr int kPer = int((uint32_t(kStageRows) * kRowUnits + kBlock - 1) / kBlock);
-            VU* lu = reinterpret_cast<VU*>(stage_u);
-            VU* lw = reinterpret_cast<VU*>(stage_w);
-            // A chunk is rows [h0, h0 + hr) of one tile; the block walks its
-            // tiles in tile_span's order. The next chunk's rows are loaded
-            // into registers while the current chunk is stored.
-            VU pu[kPer], pw[kPer];
-            auto tile_rows = [&](uint32_t tile) {
-                return dim - tile * kBlock < uint32_t(kBlock) ? dim - tile * kBlock : uint32_t(kBlock);
-            };
-            auto chunk_units = [&](uint32_t tile, uint32_t h0) {
-                const uint32_t left = tile_rows(tile) - h0;
-                return (left < uint32_t(kStageRows) ? left : uint32_t(kStageRows)) * kRowUnits;
-            };
-            auto fetch = [&](uint32_t tile, uint32_t h0) {
-                const uint32_t n = chunk_units(tile, h0);
-                const uint64_t r0 = uint64_t(tile) * kBlock + h0;
-                const VU FTLM_GLOBAL* gu = gptr(reinterpret_cast<const VU*>(u + r0 * VB));
-                const VU FTLM_GLOBAL* gw = gptr(reinterpret_cast<const VU*>(w + r0 * VB));
+        // copy unit: 16 bytes, or 8 for rows of an odd number of 8-byte words
+        constexpr int kUnit = (VB * sizeof(T)) % 16 == 0 ? 4 : 2;
+        using VU = uint32_t __attribute__((ext_vector_type(kUnit)));
+        constexpr uint32_t kRowUnits = uint32_t(VB * sizeof(T)) / uint32_t(4 * kUnit);
+        constexpr int kPer = int((uint32_t(kStageRows) * kRowUnits + kBlock - 1) / kBlock);
+        VU* lu = reinterpret_cast<VU*>(stage_u);
+        VU* lw = reinterpret_cast<VU*>(stage_w);
+        // A chunk is rows [h0, h0 + hr) of one tile; the block walks its
+        // tiles in tile_span's order. The next chunk's rows are loaded
+        // into registers while the current chunk is stored.
+        VU pu[kPer], pw[kPer];
+        auto tile_rows = [&](uint32_t tile) {
+            return dim - tile * kBlock < uint32_t(kBlock) ? dim - tile * kBlock : uint32_t(kBlock);
+        };
+        auto chunk_units = [&](uint32_t tile, uint32_t h0) {
+            const uint32_t left = tile_rows(tile) - h0;
+            return (left < uint32_t(kStageRows) ? left : uint32_t(kStageRows)) * kRowUnits;
+        };
+        auto fetch = [&](uint32_t tile, uint32_t h0) {
+            const uint32_t n = chunk_units(tile, h0);
+            const uint64_t r0 = uint64_t(tile) * kBlock + h0;
+            const VU FTLM_GLOBAL* gu = gptr(reinterpret_cast<const VU*>(u + r0 * VB));
+            const VU FTLM_GLOBAL* gw = gptr(reinterpret_cast<const VU*>(w + r0 * VB));
 #pragma unroll
-                for (int k = 0; k < kPer; ++k) {
-                    const uint32_t i = threadIdx.x + uint32_t(k) * kBlock;
-                    if (i < n) {
-                        pu[k] = __builtin_nontemporal_load(gu + i);
-                        pw[k] = __builtin_nontemporal_load(gw + i);
-                    }
+            for (int k = 0; k < kPer; ++k) {
+                const uint32_t i = threadIdx.x + uint32_t(k) * kBlock;
+                if (i < n) {
+                    pu[k] = __builtin_nontemporal_load(gu + i);
+                    pw[k] = __builtin_nontemporal_load(gw + i);
                 }
-            };
-            const TileSpan sp = tile_span(ntiles, local, sw.G);
-            uint32_t tile = sp.first, h0 = 0;
-            if (tile < sp.end) fetch(tile, h0);
-            while (tile < sp.end) {
-                const uint32_t n = chunk_units(tile, h0);
-                const uint32_t hr = n / kRowUnits;
-#pragma unroll
-                for (int k = 0; k < kPer; ++k) {
-                    const uint32_t i = threadIdx.x + uint32_t(k) * kBlock;
-                    if (i < n) {
-                        lu[i] = pu[k];
-                        lw[i] = pw[k];
-                    }
-                }
-                __syncthreads();
-                // each thread updates the row it owns (row threadIdx.x of the tile)
-                if (threadIdx.x >= h0 && threadIdx.x < h0 + hr) {
-                    T* wr = stage_w + (threadIdx.x - h0) * VB;
-                    const T* ur = stage_u + (threadIdx.x - h0) * VB;
-#pragma unroll
-                    for (int c = 0; c < VB; ++c) {
-                        const T v = wr[c] - coef[c] * ur[c];
-                        part[c] += double(v) * double(v);
-                        wr[c] = v;
-                    }
-                }
-                __syncthreads();
-                VU FTLM_GLOBAL* gw = gptr(reinterpret_cast<VU*>(w + (uint64_t(tile) * kBlock + h0) * VB));
-                h0 += uint32_t(kStageRows);
-                if (h0 >= tile_rows(tile)) {
-                    h0 = 0;
-                    tile += sp.step;
-                }
-                if (tile < sp.end) fetch(tile, h0);
-                for (uint32_t i = threadIdx.x; i < n; i += kBlock) __builtin_nontemporal_store(lw[i], gw + i);
-                __syncthreads();
             }
-        }
-    }
-    for_each_span_tile(ntiles, local, sw.G, [&](uint32_t tile) {
-        const uint32_t t = tile * kBlock + threadIdx.x;
-        if constexpr (kStage) {
-            if (staged) return;  // done above
-        }
-        if (t >= dim) return;
-        T uu[VB], ww[VB];
-        load_row<T, VB>(u + uint64_t(t) * a.ld + a.col0, uu);
-        T* wrow = w + uint64_t(t) * a.ld + a.col0;
-        load_row<T, VB>(wrow, ww);
+        };
+        const TileSpan sp = tile_span(ntiles, local, sw.G);
+        uint32_t tile = sp.first, h0 = 0;
+        if (tile < sp.end) fetch(tile, h0);
+        while (tile < sp.end) {
+            const uint32_t n = chunk_units(tile, h0);
+            const uint32_t hr = n / kRowUnits;
 #pragma unroll
-        for (int c = 0; c < VB; ++c) {
-            ww[c] = ww[c] - coef[c] * uu[c];
-            part[c] += double(ww[c]) * double(ww[c]);
+            for (int k = 0; k < kPer; ++k) {
+                const uint32_t i = threadIdx.x + uint32_t(k) * kBlock;
+                if (i < n) {
+                    lu[i] = pu[k];
+                    lw[i] = pw[k];
+                }
+            }
+            __syncthreads();
+            // each thread updates the row it owns (row threadIdx.x of the tile)
+            if (threadIdx.x >= h0 && threadIdx.x < h0 + hr) {
+                T* wr = stage_w + (threadIdx.x - h0) * VB;
+                const T* ur = stage_u + (threadIdx.x - h0) * VB;
+#pragma unroll
+                for (int c = 0; c < VB; ++c) {
+                    const T v = wr[c] - coef[c] * ur[c];
+                    part[c] += double(v) * double(v);
+                    wr[c] = v;
+                }
+            }
+            __syncthreads();
+            VU FTLM_GLOBAL* gw = gptr(reinterpret_cast<VU*>(w + (uint64_t(tile) * kBlock + h0) * VB));
+            h0 += uint32_t(kStageRows);
+            if (h0 >= tile_rows(tile)) {
+                h0 = 0;
+                tile += sp.step;
+            }
+            if (tile < sp.end) fetch(tile, h0);
+            for (uint32_t i = threadIdx.x; i < n; i += kBlock) __builtin_nontemporal_store(lw[i], gw + i);
+            __syncthreads();
         }
-        store_row<T, VB>(wrow, ww);
-    });
+    } else {
+        for_each_span_tile(ntiles, local, sw.G, [&](uint32_t tile) {
+            const uint32_t t = tile * kBlock + threadIdx.x;
+            if (t >= dim) return;
+            T uu[VB], ww[VB];
+            load_row<T, VB>(u + uint64_t(t) * VB, uu);
+            T* wrow = w + uint64_t(t) * VB;
+            load_row<T, VB>(wrow, ww);
+#pragma unroll
+            for (int c = 0; c < VB; ++c) {
+                ww[c] = ww[c] - coef[c] * uu[c];
+                part[c] += double(ww[c]) * double(ww[c]);
+            }
+            store_row<T, VB>(wrow, ww);
+        });
+    }
     __syncthreads();
     block_sum<VB>(part, red, sw.partials + size_t(local) * a.ld + a.col0, VB);
     if (last_block(sw.ticket, sw.G, &flag)) {

@@ -119,8 +119,8 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
                 cur = s;
                 const int step = uniform(sw.state[0]);
                 S = uniform(sw.S);
-                x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
-                y = uniform(static_cast<T*>(sw.u[step & 1]));
+                x = uniform(block_of<T>(a, sw.u[(step - 1) & 1], S.dim));
+                y = uniform(block_of<T>(a, sw.u[step & 1], S.dim));
                 first = step == 1;
                 stage_bonds(B, sw.bonds, NT);
                 stage_epilogue<T, VB>(ab, sw.chains + a.col0);
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
                 const uint32_t t0 = uint32_t(r0);
                 const uint32_t end = S.dim - t0 < part * 64u ? S.dim : t0 + part * 64u;
                 if constexpr (kRuns) {
-                    const unsigned char* xb = reinterpret_cast<const unsigned char*>(x + a.col0);
+                    const unsigned char* xb = reinterpret_cast<const unsigned char*>(x);
                     Run<L> run;
                     RunBonds<T> rb;
                     run.base = run.size = 0;
@@ -153,11 +153,11 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
                             lo = pos;
                             if (pos - run.base >= run.size) {
                                 run.find(pos, S, C, a.low_bits, lane);
-                                rb.load(run, B, 0, a.low_bits, lane, xb, uint32_t(a.ld * sizeof(T)), S.dim - 1);
+                                rb.load(run, B, 0, a.low_bits, lane, xb, VB * sizeof(T), S.dim - 1);
                             }
                             const uint32_t lim = stop - run.base < run.size ? stop : run.base + run.size;
-                            run_block<L, T, VB, R, kRunGroup, kEpiLanczos>(S, B, smem, a.low_bits, run, rb, x, y, a.ld,
-                                                                           a.col0, 0, p0, pos, lim, ab, first, prod);
+                            run_block<L, T, VB, R, kRunGroup, kEpiLanczos>(S, B, smem, a.low_bits, run, rb, x, y, VB, 0,
+                                                                           0, p0, pos, lim, ab, first, prod);
                             pos = lim;
                         }
                         // rows of several runs: the products of the earlier
@@ -170,8 +170,8 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
                                 const uint32_t t = p0 + uint32_t(64 * i + lane);
                                 if (t >= p0 && t < lo) {
                                     T u[VB], w[VB];
-                                    load_row<T, VB>(x + uint64_t(t) * a.ld + a.col0, u);
-                                    load_row<T, VB>(y + uint64_t(t) * a.ld + a.col0, w);
+                                    load_row<T, VB>(x + uint64_t(t) * VB, u);
+                                    load_row<T, VB>(y + uint64_t(t) * VB, w);
 #pragma unroll
                                     for (int c = 0; c < VB; ++c) prod[i][c] = double(u[c]) * double(w[c]);
                                 }
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
 #pragma unroll
                         for (int c = 0; c < VB; ++c) prod[c] = 0.0;
                         if (p0 + uint32_t(lane) < stop)
-                            walk_row<L, PATH, T, VB>(p0 + uint32_t(lane), S, B, C, ylds, x, y, a.ld, a.col0, ab, first,
+                            walk_row<L, PATH, T, VB>(p0 + uint32_t(lane), S, B, C, ylds, x, y, VB, 0, ab, first,
                                                      prod);
                         wave_fold_columns<VB, false>(prod, sums);
                         sums += VB;

@@ -14,7 +14,7 @@ constexpr size_t kSmallLds = 144 * 1024;  // most dynamic LDS: the rest of the 1
 // the persistent kernels. One workgroup runs an item on VB of the launch's
 // columns (blockIdx.y): the item's tiles go to four groups of four waves at a
 // time, each tile's sums per wave are kept apart and added in the tiles' order.
-// So neither the threads nor the columns' split change a result. setup(S, col0)
+// So neither the threads nor the columns' split change a result. setup(S, c0)
 // stages LDS and returns row(t, x, y, ab, first, prod), which writes row t and
 // its products.
 //
@@ -36,11 +36,11 @@ __device__ __forceinline__ void small_lanczos(LanczosLaunch& a, BondTable& B, un
     if (running) {
         const int step = uniform(sw.state[0]);
         const SectorDev S = uniform(sw.S);
-        const T* x = uniform(static_cast<const T*>(sw.u[(step - 1) & 1]));
-        T* y = uniform(static_cast<T*>(sw.u[step & 1]));
+        const T* x = uniform(block_of<T>(a, sw.u[(step - 1) & 1], S.dim));
+        T* y = uniform(block_of<T>(a, sw.u[step & 1], S.dim));
         stage_bonds(B, sw.bonds, kSmallThreads);
         stage_epilogue<T, VB>(ab, sw.chains + col0);
-        const auto row = setup(S, col0);
+        const auto row = setup(S, col0 - a.block0);
         __syncthreads();
         double sum = 0.0;  // thread t < kWaves VB: wave t / VB, column t % VB
         const uint32_t ntiles = (S.dim + kBlock - 1) / kBlock;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kSmallThreads) void hv_small_lanczos_kernel(Lanczos
     small_lanczos<double, VB>(a, B, smem, [&](const SectorDev& S, uint32_t col0) {
         const HvLds l = hv_lds_setup<MODE>(smem, S);
         return [=](uint32_t t, const double* x, double* y, const double* ab, bool first, double (&prod)[VB]) {
-            walk_row<L, MODE, double, VB>(t, S, B, Binom{l.binom, S.bw}, l.ylds, x, y, a.ld, col0, ab, first, prod);
+            walk_row<L, MODE, double, VB>(t, S, B, Binom{l.binom, S.bw}, l.ylds, x, y, a.block_ld, col0, ab, first, prod);
         };
     });
 }

@@ -349,7 +349,7 @@ int ftlm_hv_rows(const ftlm_sector* s, const ftlm_graph* g, const void* x_dev, v
     h.row0 = uint32_t(row0);
     h.nrows = uint32_t(nrows);
     h.dtype = dtype;
-    for (auto [col, vb] : column_chunks(nvec, uint64_t(nvec), dtype, {x_dev, y_dev}, max_launch_width(s->two_s))) {
+    for (auto [col, vb] : column_chunks(nvec, dtype, max_launch_width(s->two_s))) {
         h.col0 = uint32_t(col);
         h.vb = vb;
         HvTimer timer(st);
@@ -562,7 +562,7 @@ int ftlm_autotune(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype, v
     };
     auto batch_ms = [&](int x) {
         double t = 0.0;
-        for (auto [col, w] : column_chunks_v(x, 0, dtype, {}, lanczos_width(s->two_s, s->n_sites, dtype)))
+        for (auto [col, w] : column_chunks(x, dtype, lanczos_width(s->two_s, s->n_sites, dtype), true))
             t += measured(w);
         return t;
     };

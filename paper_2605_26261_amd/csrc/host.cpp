@@ -55,12 +55,14 @@ uint64_t stream_key(uint64_t seed, int n_up, uint64_t r) {
 
 Stats g_stats;
 
-// ---- column chunking of a [D][ld] block --------------------------------------
+// ---- column chunking ------------------------------------------------------------
 // Splits columns [0, nvec) into kernel widths of at most max_width, widest
-// first, keeping every vector access naturally aligned (ld, col0 and the base
-// pointers; ld = 0 for columns kept launch by launch, see block_of).
-std::vector<std::pair<int, int>> column_chunks_v(int nvec, uint64_t ld, int dtype, const std::vector<const void*>& ptrs,
-                                                 int max_width) {
+// first. The columns of a chunk need no more than the alignment of one element,
+// except that their first one keeps the chunk's vector accesses aligned where a
+// chunk is a block of its own (`blocks`, see block_of) that the update copies in
+// units of 16 bytes: then every one of `ptrs`, where the blocks begin, must be too.
+std::vector<std::pair<int, int>> column_chunks(int nvec, int dtype, int max_width, bool blocks,
+                                               const std::vector<const void*>& ptrs) {
     const size_t es = dtype == FTLM_F32 ? 4 : 8;
     static const int w32[] = {32, 20, 16, 12, 10, 8, 4, 2, 1};
     static const int w64[] = {16, 8, 4, 2, 1};
@@ -72,12 +74,14 @@ std::vector<std::pair<int, int>> column_chunks_v(int nvec, uint64_t ld, int dtyp
         for (int i = 0; i < nw; ++i) {
             const int vb = widths[i];
             if (vb > nvec - col || (vb > max_width && vb > 1)) continue;
-            size_t vbytes = es;
-            if (es == 4 && vb % 4 == 0) vbytes = 16;
-            else if (vb % 2 == 0) vbytes = 2 * es;
-            bool aligned = (ld * es) % vbytes == 0 && (size_t(col) * es) % vbytes == 0;
-            for (const void* p : ptrs) aligned = aligned && (reinterpret_cast<uintptr_t>(p) % vbytes == 0);
-            if (!aligned) continue;
+            if (blocks) {
+                size_t vbytes = es;
+                if (es == 4 && vb % 4 == 0) vbytes = 16;
+                else if (vb % 2 == 0) vbytes = 2 * es;
+                bool aligned = (size_t(col) * es) % vbytes == 0;
+                for (const void* p : ptrs) aligned = aligned && (reinterpret_cast<uintptr_t>(p) % vbytes == 0);
+                if (!aligned) continue;
+            }
             out.emplace_back(col, vb);
             col += vb;
             break;
@@ -86,18 +90,13 @@ std::vector<std::pair<int, int>> column_chunks_v(int nvec, uint64_t ld, int dtyp
     return out;
 }
 
-std::vector<std::pair<int, int>> column_chunks(int nvec, uint64_t ld, int dtype,
-                                               std::initializer_list<const void*> ptrs, int max_width) {
-    return column_chunks_v(nvec, ld, dtype, std::vector<const void*>(ptrs), max_width);
-}
-
 std::vector<std::pair<int, int>> job_chunks(const LanczosJob& job, int max_width) {
     std::vector<const void*> ptrs;
     for (const auto& w : job.secs) {
         ptrs.push_back(w.u[0]);
         ptrs.push_back(w.u[1]);
     }
-    return column_chunks_v(job.R, 0, job.dtype, ptrs, max_width);
+    return column_chunks(job.R, job.dtype, max_width, true, ptrs);
 }
 
 int check_dtype(int dtype) {

@@ -111,10 +111,8 @@ struct HvTimer {
     }
 };
 
-std::vector<std::pair<int, int>> column_chunks_v(int nvec, uint64_t ld, int dtype, const std::vector<const void*>& ptrs,
-                                                 int max_width = 32);
-std::vector<std::pair<int, int>> column_chunks(int nvec, uint64_t ld, int dtype, std::initializer_list<const void*> ptrs,
-                                               int max_width = 32);
+std::vector<std::pair<int, int>> column_chunks(int nvec, int dtype, int max_width, bool blocks = false,
+                                               const std::vector<const void*>& ptrs = {});
 // Widest launch of the H.x kernels of a sector: 8 columns for general spin.
 inline int max_launch_width(int two_s) { return two_s > 1 ? 8 : 32; }
 // Columns of a Lanczos launch at most. Large sectors are bound by the partner

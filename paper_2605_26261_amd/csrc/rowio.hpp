@@ -5,11 +5,15 @@
 
 namespace ftlm {
 
-// Loads/stores VB consecutive elements with the widest naturally aligned
-// vector access (the host only picks a vector width whose alignment holds),
-// as global-memory accesses.
+// Loads/stores VB consecutive elements with 16- or 8-byte accesses to global
+// memory, which need the alignment of one element only (rows of 5 or 7 columns
+// begin anywhere).
 template <typename T, int N>
-using VecT = T __attribute__((ext_vector_type(N)));
+struct VecOf {
+    typedef T type __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+};
+template <typename T, int N>
+using VecT = typename VecOf<T, N>::type;
 
 template <typename T, int VB>
 __device__ __forceinline__ void load_row(const T* __restrict__ p, T (&v)[VB]) {

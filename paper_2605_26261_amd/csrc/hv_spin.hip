@@ -338,11 +338,11 @@ __global__ __launch_bounds__(kBlock) void hv_spin_runs_kernel(SectorDev S, BondT
 }
 
 // The Lanczos step's H.x of a small sector (small_lanczos_items).
-template <int MODE, typename T, int VB>
-__global__ __launch_bounds__(kSmallThreads) void hv_spin_small_lanczos_kernel(LanczosLaunch a) {
+template <int MODE, typename T, int VB, int NT>
+__global__ __launch_bounds__(NT) void hv_spin_small_lanczos_kernel(LanczosLaunch a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ BondTable B;
-    small_lanczos<T, VB>(a, B, smem, [&](const SectorDev& S, uint32_t col0) {
+    small_lanczos<T, VB, NT>(a, B, smem, [&](const SectorDev& S, uint32_t col0) {
         const SpinLds l = spin_lds_setup<MODE>(smem, S);
         return [=](uint32_t t, const T* x, T* y, const T* ab, bool first, double (&prod)[VB]) {
             T acc[VB], xt[VB], out[VB];
@@ -585,14 +585,15 @@ hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch
 
 hipError_t launch_hv_lanczos_spin(const LanczosLaunch& a, size_t lds, hipStream_t st) {
     if (!a.queue || a.items <= 0) return hipErrorInvalidValue;  // the queue counters are required
-    const size_t small = small_lanczos_lds(lds, 2 * hv_slab_lds_bytes(a.n_sites, a.mode));
+    const size_t small = small_lanczos_lds(a, lds, 2 * hv_slab_lds_bytes(a.n_sites, a.mode));
     if (by_small_lanczos(a, small)) {
         auto narrow = [&](auto tt, auto mm) {
             using T = decltype(tt);
             constexpr int MODE = decltype(mm)::value;
-            return with_small_vb(a, [&](auto vb) {
-                return launch_small_lanczos(hv_spin_small_lanczos_kernel<MODE, T, decltype(vb)::value>,
-                                            decltype(vb)::value, a, small, st);
+            return with_small_shape(a, [&](auto vb, auto nt) {
+                constexpr int VB = decltype(vb)::value;
+                return launch_small_lanczos(hv_spin_small_lanczos_kernel<MODE, T, VB, decltype(nt)::value>, VB, a, small,
+                                            st);
             });
         };
         const auto cr = std::integral_constant<int, kModeCr>{};

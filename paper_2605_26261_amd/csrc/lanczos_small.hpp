@@ -6,13 +6,12 @@
 
 namespace ftlm {
 
-constexpr int kSmallThreads = 1024;
 constexpr int kSmallItems = 256;
 constexpr size_t kSmallLds = 144 * 1024;  // most dynamic LDS: the rest of the 160 KB holds the static arrays
 
 // The items of the launch's sector, their slots and their sums are those of
 // the persistent kernels. One workgroup runs an item on VB of the launch's
-// columns (blockIdx.y): the item's tiles go to four groups of four waves at a
+// columns (blockIdx.y): the item's tiles go to NT / 256 groups of four waves at a
 // time, each tile's sums per wave are kept apart and added in the tiles' order.
 // So neither the threads nor the columns' split change a result. setup(S, c0)
 // stages LDS and returns row(t, x, y, ab, first, prod), which writes row t and
@@ -22,9 +21,9 @@ constexpr size_t kSmallLds = 144 * 1024;  // most dynamic LDS: the rest of the 1
 // gathers in turn). The persistent kernel made four such passes in a row in one
 // workgroup per item, on 80 of the 256 CUs for 73,789 rows (icosahedron, s = 1,
 // 8 FP64 columns: Lanczos step 93.7 -> 54.8 us; 28,314 rows: 73.7 -> 30.7).
-template <typename T, int VB, typename Setup>
+template <typename T, int VB, int NT, typename Setup>
 __device__ __forceinline__ void small_lanczos(LanczosLaunch& a, BondTable& B, unsigned char* smem, Setup&& setup) {
-    constexpr uint32_t kGroups = kSmallThreads / kBlock;
+    constexpr uint32_t kGroups = NT / kBlock;
     __shared__ int flag;
     __shared__ T ab[2 * VB];
     __shared__ double psum[2][kGroups][kWaves * VB];
@@ -38,7 +37,7 @@ __device__ __forceinline__ void small_lanczos(LanczosLaunch& a, BondTable& B, un
         const SectorDev S = uniform(sw.S);
         const T* x = uniform(block_of<T>(a, sw.u[(step - 1) & 1], S.dim));
         T* y = uniform(block_of<T>(a, sw.u[step & 1], S.dim));
-        stage_bonds(B, sw.bonds, kSmallThreads);
+        stage_bonds(B, sw.bonds, NT);
         stage_epilogue<T, VB>(ab, sw.chains + col0);
         const auto row = setup(S, col0 - a.block0);
         __syncthreads();
@@ -86,11 +85,11 @@ __device__ __forceinline__ void small_lanczos(LanczosLaunch& a, BondTable& B, un
 }
 
 // Spin 1/2, FP64 vectors.
-template <typename L, int MODE, int VB>
-__global__ __launch_bounds__(kSmallThreads) void hv_small_lanczos_kernel(LanczosLaunch a) {
+template <typename L, int MODE, int VB, int NT>
+__global__ __launch_bounds__(NT) void hv_small_lanczos_kernel(LanczosLaunch a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ BondTable B;
-    small_lanczos<double, VB>(a, B, smem, [&](const SectorDev& S, uint32_t col0) {
+    small_lanczos<double, VB, NT>(a, B, smem, [&](const SectorDev& S, uint32_t col0) {
         const HvLds l = hv_lds_setup<MODE>(smem, S);
         return [=](uint32_t t, const double* x, double* y, const double* ab, bool first, double (&prod)[VB]) {
             walk_row<L, MODE, double, VB>(t, S, B, Binom{l.binom, S.bw}, l.ylds, x, y, a.block_ld, col0, ab, first, prod);
@@ -98,17 +97,19 @@ __global__ __launch_bounds__(kSmallThreads) void hv_small_lanczos_kernel(Lanczos
     });
 }
 
+// Threads of a workgroup: up to seven items have one tile each and four waves
+// do; else sixteen, four tiles at a time.
+inline int small_threads(const LanczosLaunch& a) { return a.items < 8 ? kBlock : 4 * kBlock; }
+
 // LDS of a small launch from a workgroup's of kBlock threads, `slabs` bytes of
 // which are its waves' own.
-inline size_t small_lanczos_lds(size_t lds, size_t slabs) {
-    return std::max(lds + slabs * (kSmallThreads / kBlock - 1), kGridSumLds);
+inline size_t small_lanczos_lds(const LanczosLaunch& a, size_t lds, size_t slabs) {
+    return std::max(lds + slabs * size_t(small_threads(a) / kBlock - 1), kGridSumLds);
 }
 
-// One sector with no more items than CUs, while the slabs of 16 waves fit. Up to
-// seven items have one tile each: four waves do (924 rows, 8 FP64 columns: 11.8
-// us a launch against 16).
+// One sector with no more items than CUs, while the slabs of its waves fit.
 inline bool by_small_lanczos(const LanczosLaunch& a, size_t lds) {
-    return a.nsec == 1 && a.items >= 8 && a.items <= kSmallItems && lds <= kSmallLds &&
+    return a.nsec == 1 && a.items <= kSmallItems && lds <= kSmallLds &&
            (a.vb <= 2 || a.vb == 4 || a.vb == 8 || a.vb == 16);
 }
 
@@ -116,7 +117,11 @@ inline bool by_small_lanczos(const LanczosLaunch& a, size_t lds) {
 // within one to a CU (73,789 rows, 80 items, 8 FP64 columns: 55 us with two
 // workgroups an item, 89 with four), at most four for the registers.
 template <typename F>
-hipError_t with_small_vb(const LanczosLaunch& a, F&& f) {
+hipError_t with_small_shape(const LanczosLaunch& a, F&& g) {
+    auto f = [&](auto vb) {
+        return small_threads(a) == kBlock ? g(vb, std::integral_constant<int, kBlock>{})
+                                          : g(vb, std::integral_constant<int, 4 * kBlock>{});
+    };
     int vb = a.vb;
     while (vb > 4 || (vb > 1 && vb % 2 == 0 && a.items * (a.vb / vb) * 2 <= kSmallItems)) vb /= 2;
     if (vb == 1) return f(std::integral_constant<int, 1>{});
@@ -132,7 +137,7 @@ hipError_t launch_small_lanczos(K kern, int vb, const LanczosLaunch& a, size_t l
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(unsigned(a.items), unsigned(a.vb / vb)), dim3(kSmallThreads), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(unsigned(a.items), unsigned(a.vb / vb)), dim3(unsigned(small_threads(a))), lds, st, a);
     return hipGetLastError();
 }
 

@@ -89,6 +89,10 @@ extern Stats g_stats;
 struct HvTimer {
     hipEvent_t a = nullptr, b = nullptr;
     hipStream_t st;
+    static bool wanted() {
+        std::lock_guard<std::mutex> lk(g_stats.mu);
+        return g_stats.on;
+    }
     explicit HvTimer(hipStream_t s) : st(s) {
         std::lock_guard<std::mutex> lk(g_stats.mu);
         if (!g_stats.on) return;

@@ -351,11 +351,7 @@ __device__ __forceinline__ void finish_alpha(const SecWork& sw, const LanczosLau
     __shared__ double tot[grid_sum_slots<VB, NT>()];
     grid_sum_cols<VB, NT, SPAN>(sw.partials, int(n), int(a.ld), int(a.col0), VB, red, tot);
     if (threadIdx.x < VB) {
-        Chain* ch = &sw.chains[a.col0 + threadIdx.x];
-        const double alpha = ch->s_cur * tot[threadIdx.x], up = alpha * ch->s_cur;
-        ch->alpha = alpha;
-        ch->up_d = up;
-        ch->up_f = float(up);
+        chain_set_alpha(&sw.chains[a.col0 + threadIdx.x], tot[threadIdx.x]);
     }
 }
 

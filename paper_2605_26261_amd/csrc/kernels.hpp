@@ -46,6 +46,14 @@ __device__ __forceinline__ void chain_set_hv(Chain* ch) {
     ch->hv_b_f = float(ch->hv_b_d);
 }
 
+// alpha_k of a chain from <u_k, w>, and the update's coefficient.
+__device__ __forceinline__ void chain_set_alpha(Chain* ch, double sum) {
+    const double alpha = ch->s_cur * sum, up = alpha * ch->s_cur;
+    ch->alpha = alpha;
+    ch->up_d = up;
+    ch->up_f = float(up);
+}
+
 // A sector as the kernels see it. Spin-1/2 sectors (two_s = 1) hold the
 // binomial table; for a local spin s = two_s / 2 > 1/2, n_up is the sector's
 // digit sum A (Eq. 17), `binom` holds the cumulative dimension table of
@@ -186,6 +194,10 @@ hipError_t launch_neighbors_spin(const SectorDev& s, const BondTable& B, uint64_
 hipError_t launch_hv_lanczos(const LanczosLaunch& a, size_t lds, hipStream_t st);
 hipError_t launch_start(const LanczosLaunch& a, hipStream_t st);
 hipError_t launch_update(const LanczosLaunch& a, hipStream_t st);
+// Every step of a launch whose sectors are all tiny, in one kernel (n_bonds: the
+// most bonds of a sector's graph).
+bool by_tiny_chains(const LanczosLaunch& a);
+hipError_t launch_tiny_chains(const LanczosLaunch& a, int n_bonds, hipStream_t st);
 hipError_t launch_chain_init(const LanczosLaunch& a, hipStream_t st);
 
 // Sector table builders and index kernels (sector.hip).

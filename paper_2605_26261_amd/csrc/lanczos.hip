@@ -45,6 +45,10 @@ hipError_t launch_hv_lanczos(const LanczosLaunch& a, size_t lds, hipStream_t st)
 
 namespace {
 
+constexpr int kTinyThreads = 1024;
+constexpr int kTinyTiles = 7;  // fewer than eight: one tile to a work item and to an update block
+constexpr size_t kTinyLds = 152 * 1024;
+
 constexpr uint64_t kGamma = 0x9e3779b97f4a7c15ull;
 
 // SplitMix64's output function (Steele, Lea, Flood 2014).
@@ -127,6 +131,38 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
             }
         }
     }
+}
+
+// beta_k = |w| of the chain in column col from |w|^2: records step k's
+// coefficients, applies the stopping rule and sets the next step's scalars.
+// Returns whether the chain stopped.
+__device__ __forceinline__ bool finish_beta(Chain* ch, const SecWork& sw, int col, int step, double norm2, double eps) {
+    if (!ch->active) return false;
+    const double bk = sqrt(norm2);
+    const double ak = ch->alpha;
+    sw.alpha[size_t(col) * kMaxSteps + (step - 1)] = ak;
+    sw.beta[size_t(col) * kMaxSteps + (step - 1)] = bk;
+    const double amax = fmax(ch->amax, fmax(fabs(ak), ch->beta_prev));
+    ch->amax = amax;
+    ch->steps = step;
+    // a non-finite coefficient ends the chain and marks it (the host reports
+    // FTLM_E_NUMERIC); the comparison below is false for NaN, so without this
+    // the chain would run on
+    const bool fault = !(isfinite(ak) && isfinite(bk));
+    if (fault) ch->fault = 1;
+    const bool stopped = fault || step >= sw.m_eff || bk <= eps * amax;
+    if (stopped) {
+        ch->active = 0;
+        ch->s_cur = 0.0;
+        ch->s_prev = 0.0;
+        ch->beta_prev = 0.0;
+    } else {
+        ch->s_prev = ch->s_cur;
+        ch->s_cur = 1.0 / bk;
+        ch->beta_prev = bk;
+    }
+    chain_set_hv(ch);
+    return stopped;
 }
 
 // Second half of Lanczos step k for columns [col0, col0 + VB) of every
@@ -287,33 +323,7 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
             bool stopped = false;
             if (threadIdx.x < VB) {
                 const int col = int(a.col0 + threadIdx.x);
-                Chain* ch = &sw.chains[col];
-                if (ch->active) {
-                    const double bk = sqrt(tot[threadIdx.x]);
-                    const double ak = ch->alpha;
-                    sw.alpha[size_t(col) * kMaxSteps + (step - 1)] = ak;
-                    sw.beta[size_t(col) * kMaxSteps + (step - 1)] = bk;
-                    const double amax = fmax(ch->amax, fmax(fabs(ak), ch->beta_prev));
-                    ch->amax = amax;
-                    ch->steps = step;
-                    // a non-finite coefficient ends the chain and marks it
-                    // (the host reports FTLM_E_NUMERIC); the comparison below
-                    // is false for NaN, so without this the chain would run on
-                    const bool fault = !(isfinite(ak) && isfinite(bk));
-                    if (fault) ch->fault = 1;
-                    stopped = fault || step >= sw.m_eff || bk <= a.eps * amax;
-                    if (stopped) {
-                        ch->active = 0;
-                        ch->s_cur = 0.0;
-                        ch->s_prev = 0.0;
-                        ch->beta_prev = 0.0;
-                    } else {
-                        ch->s_prev = ch->s_cur;
-                        ch->s_cur = 1.0 / bk;
-                        ch->beta_prev = bk;
-                    }
-                    chain_set_hv(ch);
-                }
+                stopped = finish_beta(&sw.chains[col], sw, col, step, tot[threadIdx.x], a.eps);
             }
             const int n = __popcll(__ballot(stopped));
             if (threadIdx.x == 0) {
@@ -323,6 +333,154 @@ __global__ __launch_bounds__(kBlock) void update_kernel(LanczosLaunch a) {
             }
         }
     }
+}
+
+// Row gathers from a vector in LDS, one column (GatherVisitor's flip).
+template <typename T>
+struct LdsGather {
+    const T* x;
+    uint32_t last;
+    const BondTable& B;
+    T& acc;
+    T& anti;
+    __device__ __forceinline__ void flip(int b, uint32_t i) {
+        const T c = bond_coef<T>(B, b);
+        acc += c * x[i < last ? i : last];
+        anti += c;
+    }
+    __device__ __forceinline__ void par(int) {}
+};
+
+// A row's partners, bond by bond (kNoPartner: the bond does not flip).
+constexpr uint32_t kNoPartner = 0xffffu;
+struct LdsPartners {
+    uint16_t* p;  // of bond 0
+    uint32_t stride, last;
+    __device__ __forceinline__ void flip(int b, uint32_t i) { p[uint32_t(b) * stride] = uint16_t(i < last ? i : last); }
+    __device__ __forceinline__ void par(int b) { p[uint32_t(b) * stride] = uint16_t(kNoPartner); }
+};
+
+// LDS of tiny_chain_kernel: both vectors, the binomial table, the Y values of
+// its waves, and the rows' partners where they fit.
+inline size_t tiny_chain_lds(uint64_t dim, int n_sites, size_t es) {
+    return 2 * ((size_t(dim) * es + 15) & ~size_t(15)) + ((size_t(n_sites) * size_t(n_sites + 3) * 4 + 15) & ~size_t(15)) +
+           size_t(kTinyThreads) * size_t(n_sites) * 4;
+}
+inline size_t tiny_partner_lds(uint64_t dim, int n_bonds) {
+    return size_t(n_bonds) * size_t((dim + 63) & ~uint64_t(63)) * 2;
+}
+
+// Every step of one chain (blockIdx.x) of one sector (blockIdx.y) of at most
+// kTinyTiles row tiles by one workgroup, both vectors in LDS from start to end.
+//
+// What bounds it: the latency of a row's gathers and of four barriers a step.
+// Step by step 924 rows (24 bonds, 8 FP64 columns) took 21 us for two launches,
+// each with its ticket and the gap after it; here a step takes 7.1 us with every
+// row walked in every step and 4.2 with the partners, the same in all steps,
+// found once (`partners`: they fit beside the rest).
+//
+// Up to seven row tiles each is a work item and a block of its own, so the sums
+// are those of the step-by-step kernels: a wave's 64 rows by fold, a tile's four
+// waves in order, the tiles by the fold of the first wave.
+template <typename L, typename T>
+__global__ __launch_bounds__(kTinyThreads) void tiny_chain_kernel(LanczosLaunch a, int partners) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ BondTable B;
+    __shared__ double psum[4 * kTinyTiles];
+    __shared__ Chain chain;
+    __shared__ double tot;
+    const SecWork& sw = a.secs[blockIdx.y];
+    const int col = int(a.col0 + blockIdx.x);
+    const SectorDev S = uniform(sw.S);
+    const uint32_t dim = S.dim, groups = 4u * ((dim + kBlock - 1) / kBlock);
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = uniform(threadIdx.x >> 6);
+    T* u0 = reinterpret_cast<T*>(smem);
+    T* u1 = reinterpret_cast<T*>(smem + ((size_t(dim) * sizeof(T) + 15) & ~size_t(15)));
+    uint32_t* binom = reinterpret_cast<uint32_t*>(smem + 2 * ((size_t(dim) * sizeof(T) + 15) & ~size_t(15)));
+    uint32_t* ylds = binom + ((S.n_sites * S.bw + 3) & ~3) + wave * uint32_t(S.n_sites) * 64u + uint32_t(lane);
+    stage_bonds(B, sw.bonds, kTinyThreads);
+    stage_binomials(binom, S.binom, S.n_sites * S.bw);
+    const T* src = block_of<T>(a, sw.u[0], dim) + (uint32_t(col) - a.block0);
+    for (uint32_t t = threadIdx.x; t < dim; t += kTinyThreads) u0[t] = *gptr(src + uint64_t(t) * a.block_ld);
+    if (threadIdx.x == 0) chain = sw.chains[col];
+    __syncthreads();
+    const Binom C{binom, S.bw};
+    const T jsum4 = sizeof(T) == 4 ? T(B.jsum4_f) : T(B.jsum4_d);
+    const uint32_t stride = (dim + 63u) & ~63u;
+    const int n_bonds = uniform(B.n_bonds);
+    uint16_t* const rows = reinterpret_cast<uint16_t*>(binom + ((S.n_sites * S.bw + 3) & ~3) + kTinyThreads * S.n_sites);
+    if (partners) {
+        for (uint32_t t = wave * 64u + uint32_t(lane); t < dim; t += kTinyThreads) {
+            LdsPartners vis{rows + t, stride, dim - 1};
+            cr_bonds<L, false>(t, L(0), S.n_up, B, C, ylds, vis);
+        }
+    }
+    // the sums of the tiles' rows from those of their waves, by the first wave
+    auto total = [&] {
+        double t[1] = {0.0};
+        if (uint32_t(lane) * 4u < groups)
+            for (int w = 0; w < 4; ++w) t[0] += psum[4 * lane + w];
+        wave_fold_columns<1, false>(t, &tot);
+        __builtin_amdgcn_wave_barrier();
+    };
+#pragma unroll 1
+    for (int step = 1; chain.active; ++step) {
+        const T* x = (step & 1) ? u0 : u1;
+        T* y = (step & 1) ? u1 : u0;
+        const T ab[2] = {sizeof(T) == 4 ? T(chain.hv_a_f) : T(chain.hv_a_d),
+                         sizeof(T) == 4 ? T(chain.hv_b_f) : T(chain.hv_b_d)};
+        for (uint32_t g = wave; g < groups; g += kTinyThreads / 64) {
+            const uint32_t t = g * 64u + uint32_t(lane);
+            double prod[1] = {0.0};
+            if (t < dim) {
+                T acc = T(0), anti = T(0);
+                if (partners) {
+#pragma unroll 4
+                    for (int b = 0; b < n_bonds; ++b) {
+                        const uint32_t i = rows[uint32_t(b) * stride + t];
+                        const bool on = i != kNoPartner;
+                        const T c = on ? bond_coef<T>(B, b) : T(0), v = x[on ? i : 0u];
+                        acc += c * (on ? v : T(0));
+                        anti += c;
+                    }
+                } else {
+                    LdsGather<T> vis{x, dim - 1, B, acc, anti};
+                    cr_bonds<L, false>(t, L(0), S.n_up, B, C, ylds, vis);
+                }
+                const T diag = jsum4 - anti, xt = x[t];
+                T out = diag * xt + acc;
+                out = ab[0] * out - ab[1] * (step == 1 ? T(0) : y[t]);
+                prod[0] = double(xt) * double(out);
+                y[t] = out;
+            }
+            wave_fold_columns<1, false>(prod, psum + g);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            total();
+            if (lane == 0) chain_set_alpha(&chain, tot);
+        }
+        __syncthreads();
+        const T up = sizeof(T) == 4 ? T(chain.up_f) : T(chain.up_d);
+        for (uint32_t g = wave; g < groups; g += kTinyThreads / 64) {
+            const uint32_t t = g * 64u + uint32_t(lane);
+            double part[1] = {0.0};
+            if (t < dim) {
+                const T v = y[t] - up * x[t];
+                part[0] += double(v) * double(v);
+                y[t] = v;
+            }
+            wave_fold_columns<1, false>(part, psum + g);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            total();
+            if (lane == 0 && finish_beta(&chain, sw, col, step, tot, a.eps)) atomicSub(&sw.state[1], 1);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) sw.chains[col] = chain;
 }
 
 // Zeroes every sector's chain states and ticket and sets its step counter to
@@ -367,6 +525,29 @@ hipError_t launch_update(const LanczosLaunch& a, hipStream_t st) {
 hipError_t launch_chain_init(const LanczosLaunch& a, hipStream_t st) {
     hipLaunchKernelGGL(chain_init_kernel, dim3(unsigned(a.nsec)), dim3(64), 0, st, a);
     return hipGetLastError();
+}
+
+hipError_t launch_tiny_chains(const LanczosLaunch& a, int n_bonds, hipStream_t st) {
+    size_t lds = tiny_chain_lds(a.max_dim, a.n_sites, a.dtype == 0 ? 4 : 8);
+    const size_t rows = tiny_partner_lds(a.max_dim, n_bonds);
+    const int partners = lds + rows <= kTinyLds ? 1 : 0;
+    if (partners) lds += rows;
+    auto go = [&](auto kern) {
+        hipError_t e = hipSuccess;
+        if (lds > 65536)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    int(lds));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3(unsigned(a.vb), unsigned(a.nsec)), dim3(kTinyThreads), lds, st, a, partners);
+        return hipGetLastError();
+    };
+    if (a.n_sites > 32) return a.dtype == 0 ? go(tiny_chain_kernel<uint64_t, float>) : go(tiny_chain_kernel<uint64_t, double>);
+    return a.dtype == 0 ? go(tiny_chain_kernel<uint32_t, float>) : go(tiny_chain_kernel<uint32_t, double>);
+}
+
+bool by_tiny_chains(const LanczosLaunch& a) {
+    return a.two_s <= 1 && a.max_dim <= uint64_t(kTinyTiles) * kBlock &&
+           tiny_chain_lds(a.max_dim, a.n_sites, a.dtype == 0 ? 4 : 8) <= kTinyLds;
 }
 
 }  // namespace ftlm

@@ -306,7 +306,9 @@ int ftlm_autotune(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype, v
  * workgroups sized by its dimension (sectors of dimension 1 to 10^6+ in the
  * same launch), and the M-step loop can be captured once in a HIP graph and
  * replayed. Per-chain results are bitwise the same as ftlm_lanczos on the
- * sector alone (the reduction order of a sector depends only on D).
+ * sector alone (the reduction order of a sector depends only on D and the
+ * vectors' type). A run whose sectors all have at most 1792 states takes one
+ * launch for all steps.
  *
  * ftlm_plan_workspace_bytes: device bytes of the arena for the sectors
  * n_ups[0..n_sectors-1] (1 <= n_sectors <= 65): sector tables, two [D][R]
@@ -502,7 +504,9 @@ int ftlm_seed_spread(int n_seeds, int n, const double* values, double* mean, dou
  * When enabled, the library records a pair of HIP events around every H.x
  * launch on the launch's own stream and accumulates their elapsed times;
  * ftlm_stats_read synchronizes on the recorded events and reports the count
- * of H.x launches and their total milliseconds since the last reset. */
+ * of H.x launches and their total milliseconds since the last reset. While
+ * enabled, runs on tiny sectors (at most 1792 states) go launch by launch,
+ * with the same results. */
 int ftlm_stats_enable(int on);
 int ftlm_stats_reset(void);
 int ftlm_stats_read(int64_t* hv_launches, double* hv_ms);

@@ -108,14 +108,20 @@ int check_dtype(int dtype) {
 
 
 
+// FP64 partials of a sector: a slot for every block of the update and every slot
+// of the H.x.
+size_t partial_bytes(uint64_t dim, int R, int dtype) {
+    size_t slots = std::max(stream_grid(uint32_t(dim)), strided_items(uint32_t(dim)));
+    if (dtype == FTLM_F32) slots = std::max(slots, size_t(sector_items(uint32_t(dim), true)));
+    return slots * size_t(R) * sizeof(double);
+}
+
 // Lays out the state of a sector of dimension `dim` at `off`; returns the end.
 size_t layout_state(uint64_t dim, int R, int dtype, size_t off, SectorState& st) {
     const size_t es = dtype == FTLM_F32 ? 4 : 8;
     st.u0 = off; off = align256(off + size_t(dim) * size_t(R) * es);
     st.u1 = off; off = align256(off + size_t(dim) * size_t(R) * es);
-    size_t slots = std::max(stream_grid(uint32_t(dim)), strided_items(uint32_t(dim)));
-    if (dtype == FTLM_F32) slots = std::max(slots, size_t(sector_items(uint32_t(dim), true)));
-    st.partials = off; off = align256(off + slots * size_t(R) * sizeof(double));
+    st.partials = off; off = align256(off + partial_bytes(dim, R, dtype));
     st.chains = off; off = align256(off + size_t(R) * sizeof(Chain));
     st.alpha = off; off = align256(off + size_t(R) * kMaxSteps * sizeof(double));
     st.beta = off; off = align256(off + size_t(R) * kMaxSteps * sizeof(double));

@@ -120,8 +120,8 @@ std::vector<std::pair<int, int>> column_chunks(int nvec, int dtype, int max_widt
 // Widest launch of the H.x kernels of a sector: 8 columns for general spin.
 inline int max_launch_width(int two_s) { return two_s > 1 ? 8 : 32; }
 // Columns of a Lanczos launch at most. Large sectors are bound by the partner
-// lines that miss L2, of which eight columns move the fewest per column (by runs
-// from 16 million rows); small ones by the launches. The line goes by the sites
+// lines that miss L2, of which up to eight columns move the fewest per column (by runs
+// from 2^26 rows); small ones by the launches. The line goes by the sites
 // alone, so that requests of one size run together whatever their sectors. 32
 // FP32 columns, a step, half filling, at most 32 / 20 or 16 / 8 columns a launch:
 // 18 sites 55 / 76 / 111 us, 20 sites 133 / 130 / 163, 21 sites 236 / 208 / 239, 22
@@ -139,6 +139,7 @@ int check_dtype(int dtype);
 struct SectorState {
     size_t u0, u1, partials, chains, alpha, beta, ticket, keys, state;
 };
+size_t partial_bytes(uint64_t dim, int R, int dtype);
 size_t layout_state(uint64_t dim, int R, int dtype, size_t off, SectorState& st);
 
 template <typename P>

@@ -15,9 +15,13 @@
 namespace {
 
 constexpr size_t kScratchBytes = FTLM_NOALLOC_SCRATCH_BYTES;
+// The consecutive slots of FP32 chains (slot_rows) take up to a thousandth more
+// than strided ones would. The limit counts the latter, so that it is the same
+// chains that fit.
+constexpr size_t kSlotBytes = size_t(64) << 10;
 constexpr int kMaxDevices = 64;
 
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kSlotBytes];
 
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, once looked up
@@ -49,11 +53,12 @@ extern "C" int ftlm_lanczos_noalloc(const ftlm_sector* s, const ftlm_graph* g, u
     if (!s || !g || !alpha_host || !beta_host || !steps_host) return fail(FTLM_E_INVALID, "null argument");
     size_t need = 0;
     if (int rc = ftlm_lanczos_workspace_bytes(s, R, dtype, &need)) return rc;
-    if (need > kScratchBytes)
+    const size_t slots = align256(partial_bytes(s->dim, R, dtype)) - align256(partial_bytes(s->dim, R, FTLM_F64));
+    if (need - slots > kScratchBytes || need > sizeof(scratch))
         return fail(FTLM_E_RANGE,
                     "R = %d chains of a sector of dimension %llu need %zu bytes of workspace; the no-alloc scratch "
                     "holds %zu",
-                    R, (unsigned long long)s->dim, need, kScratchBytes);
+                    R, (unsigned long long)s->dim, need - slots, kScratchBytes);
     int dev = -1;
     void* work = nullptr;
     if (int rc = scratch_on_current_device(&dev, &work)) return rc;
@@ -62,6 +67,6 @@ extern "C" int ftlm_lanczos_noalloc(const ftlm_sector* s, const ftlm_graph* g, u
     HIP_CHECK(hipPointerGetAttributes(&attr, s->table));
     if (attr.device != dev)
         return fail(FTLM_E_INVALID, "sector tables are on device %d, the current device is %d", attr.device, dev);
-    return ftlm_lanczos(s, g, seed, r0, R, M, dist, dtype, work, kScratchBytes, alpha_host, beta_host, steps_host,
+    return ftlm_lanczos(s, g, seed, r0, R, M, dist, dtype, work, sizeof(scratch), alpha_host, beta_host, steps_host,
                         stream);
 }

@@ -273,7 +273,8 @@ int ftlm_server::round() {
         }
         g.grid = int(block);
         g.items = int(items);
-        // equal R and 256-byte aligned blocks give every member the same chunks
+        // equal N, R and type and 256-byte aligned blocks give every member the
+        // same chunks, in which its vectors lie (block_of)
         g.chunks = reqs[0]->job.chunks;
         g.dev_secs = desc + slot;
         g.queue = queue();

@@ -41,7 +41,7 @@ LAUNCH_WIDTHS_F32 = (1, 2, 4, 8, 10, 12, 16, 20, 32)
 # includes the Infinity Cache, so this bounds the HBM traffic from above.
 # They describe the kernel sources with this hash and are dropped otherwise.
 KERNEL_SOURCES = ["layout.hpp", "device.hpp", "kernels.hpp", "rowloop.hpp", "rowio.hpp", "lowtab.hpp", "runs.hpp",
-                  "hv_impl.hpp", "hv_f32.hip"]
+                  "hv_impl.hpp", "lanczos_rows.hpp", "hv_lanczos_f32.hip"]
 MEASURED_TRAFFIC = {"sources": "1123cd4f9861cbbe", "bytes": {
     "clt": {1: 19.44e9, 2: 34.19e9, 4: 65.48e9, 8: 125.77e9, 10: 160.94e9, 12: 197.3e9, 16: 272.91e9, 20: 340.19e9},
     "cr": {1: 13.41e9, 2: 26.88e9, 4: 55.84e9, 8: 112.51e9, 10: 153.01e9, 12: 190.25e9, 16: 250.94e9, 20: 338.26e9},
@@ -62,34 +62,11 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def clt_touched_bytes(n, n_up):
-    """Bytes of the non-empty compressed-lookup-table blocks: block b holds
-    sector labels iff 0 <= n_up - popcount(b) <= 5."""
-    blocks = sum(math.comb(n - 5, k) for k in range(max(0, n_up - 5), min(n - 5, n_up) + 1))
-    return 8 * blocks
-
-
-def map_bytes(mode, dim, n, n_up):
-    """Bytes of the stored index map a launch must read at least once: the
-    basis (4 D) and the touched part of the map: the non-empty CLT blocks,
-    the D sector entries of the full table, or both Lin tables."""
-    if mode == "cr":
-        return 0
-    b = 4 * dim
-    if mode == "clt":
-        b += clt_touched_bytes(n, n_up)
-    elif mode == "full":
-        b += 4 * dim
-    elif mode == "lin":
-        lo = n // 2
-        b += 4 * ((1 << (n - lo)) + (1 << lo))
-    return b
-
-
-def hv_alg_bytes(mode, dim, nvec, n, n_up):
+def hv_alg_bytes(dim, nvec):
     """Algorithmic HBM bytes of one Lanczos-epilogue H.x launch over nvec FP32
-    columns: read x (u_k) and z (u_{k-1}), write w, plus the stored map."""
-    return 12 * dim * nvec + map_bytes(mode, dim, n, n_up)
+    columns: read x (u_k) and z (u_{k-1}), write w. A stored map is not counted:
+    at this size the library ranks in sectors that hold one, too."""
+    return 12 * dim * nvec
 
 
 def timed_hv(ftlm, torch, sec, g, x, y, reps):
@@ -163,20 +140,25 @@ def run_gpu(args):
         ftlm.stats_enable(False)
         launches, hv_ms = ftlm.stats_read()
         # every batch launches M = min(M, D) steps
-        job_alg = args.steps * M * sum(hv_alg_bytes(mode_name, dim, b, N_SITES, N_UP) for _, b in batches)
-        # the H.x of one batch of B chains alone: the roofline's launch
-        ftlm.lanczos(sec, g, SEED, 0, B, 2, ftlm.GAUSS, ftlm.F32, work=work)
-        torch.cuda.synchronize()
-        ftlm.stats_reset()
-        ftlm.stats_enable(True)
-        ftlm.lanczos(sec, g, SEED, 0, B, 12, ftlm.GAUSS, ftlm.F32, work=work)
-        torch.cuda.synchronize()
-        ftlm.stats_enable(False)
-        nb, msb = ftlm.stats_read()
+        job_alg = args.steps * M * sum(hv_alg_bytes(dim, b) for _, b in batches)
+        # the roofline's launch: the widest one that a batch of B chains takes
+        # (a batch may take several; at `width` chains a step is one launch)
+        for width in sorted((w for w in LAUNCH_WIDTHS_F32 if w <= B), reverse=True):
+            ftlm.lanczos(sec, g, SEED, 0, width, 2, ftlm.GAUSS, ftlm.F32, work=work)
+            torch.cuda.synchronize()
+            ftlm.stats_reset()
+            ftlm.stats_enable(True)
+            ftlm.lanczos(sec, g, SEED, 0, width, 12, ftlm.GAUSS, ftlm.F32, work=work)
+            torch.cuda.synchronize()
+            ftlm.stats_enable(False)
+            nb, msb = ftlm.stats_read()
+            if nb == 12:
+                break
         avg_ms = msb / nb
-        alg = hv_alg_bytes(mode_name, dim, B, N_SITES, N_UP)
+        alg = hv_alg_bytes(dim, width)
         results[mode_name] = {
             "batch": B,
+            "launch_width": width,
             "autotune_ms": tuned,
             "seconds": dt,
             "ms_per_step": 1e3 * dt / args.steps,
@@ -185,7 +167,7 @@ def run_gpu(args):
             "hv_launches": launches,
             "hv_job_alg_gbs": job_alg / (hv_ms * 1e-3) / 1e9,
             "hv_avg_ms": avg_ms,
-            "hv_kernel_states_bonds_per_s": dim * n_bonds * B / (avg_ms * 1e-3),
+            "hv_kernel_states_bonds_per_s": dim * n_bonds * width / (avg_ms * 1e-3),
             "hv_alg_bytes": alg,
             "hv_alg_gbs": alg / (avg_ms * 1e-3) / 1e9,
             "E0": float(rec["theta"][rec["theta"] != 0].min()),
@@ -199,7 +181,7 @@ def run_gpu(args):
             x = torch.randn((dim, nv) if nv > 1 else (dim,), dtype=torch.float32, device=dev)
             y = torch.empty_like(x)
             ms = timed_hv(ftlm, torch, sec, g, x, y, 20)
-            a = 8 * dim * nv + map_bytes(mode_name, dim, N_SITES, N_UP)  # read x, write y, read the map
+            a = 8 * dim * nv  # read x, write y
             sweep[str(nv)] = {"ms": ms, "states_bonds_per_s": dim * n_bonds * nv / (ms * 1e-3),
                               "alg_gbs": a / (ms * 1e-3) / 1e9}
             del x, y
@@ -741,13 +723,13 @@ def main():
     dom = results[best]
     traffic = None
     if kernel_source_hash() == MEASURED_TRAFFIC["sources"]:
-        traffic = MEASURED_TRAFFIC["bytes"].get(best, {}).get(dom["batch"])
+        traffic = MEASURED_TRAFFIC["bytes"].get(best, {}).get(dom["launch_width"])
     roof = {"bound": "hbm", "achieved": dom["hv_alg_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": dom["hv_alg_gbs"] / HBM_PEAK_GBS, "traffic": traffic,
             "traffic_unit": "bytes per launch between L2 and the memory side (2 x FETCH_SIZE + WRITE_SIZE, "
                             "copy-calibrated; includes Infinity Cache hits)",
-            "kernel": f"hv_lanczos_kernel<uint32, {best.upper()}, float, {dom['batch']}> (Lanczos-epilogue H.x "
-                      f"over {dom['batch']} FP32 columns)",
+            "kernel": f"lanczos_rows_kernel<uint32, float, {dom['launch_width']}> (Lanczos-epilogue H.x "
+                      f"over {dom['launch_width']} FP32 columns)",
             "alg_bytes_per_launch": dom["hv_alg_bytes"], "avg_launch_ms": dom["hv_avg_ms"]}
     # counted HBM traffic of the same launch over its measured duration
     counted_gbs = traffic / (dom["hv_avg_ms"] * 1e-3) / 1e9 if traffic else None

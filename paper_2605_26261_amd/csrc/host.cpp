@@ -214,9 +214,9 @@ int job_start(LanczosJob& job, uint64_t seed, uint64_t r0, int dist, hipStream_t
     for (auto [col, width] : job.chunks) {
         a.block0 = uint32_t(col);
         a.block_ld = uint32_t(width);
-        for (int c = 0; c < width; c += 4) {
+        for (int c = 0; c < width; c += 8) {
             a.col0 = uint32_t(col + c);
-            a.vb = std::min(4, width - c);
+            a.vb = std::min(8, width - c);
             HIP_CHECK(launch_start(a, st));
         }
     }

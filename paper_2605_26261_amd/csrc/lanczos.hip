@@ -75,7 +75,12 @@ __device__ __forceinline__ double start_entry(int dist, uint64_t key, uint64_t i
 
 // Writes columns [col0, col0 + vb) (vb <= CB) of every sector's start block
 // u_1 and their FP64 norms; the last block of a sector turns the norms into
-// each chain's initial scale s_1 = 1 / |u_1|.
+// each chain's initial scale s_1 = 1 / |u_1|. Bound by the arithmetic of an entry
+// (FP64 log and cos of a Gaussian: 8 columns at N = 30 10.6 ms, 12.3 with a store
+// per entry and the key read again for each), or by the launches: up to eight
+// columns go together and a row is stored with wide accesses (9.7 million rows of
+// 32 signs: 1.27 -> 0.51 ms). One column to four waves was slower (17.8 ms, 4-byte
+// stores of four waves to each line).
 template <typename T, int CB>
 __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
     __shared__ double red[grid_sum_lds<CB>() / sizeof(double)];
@@ -90,19 +95,29 @@ __global__ __launch_bounds__(kBlock) void start_kernel(LanczosLaunch a) {
     double part[CB];
 #pragma unroll
     for (int c = 0; c < CB; ++c) part[c] = 0.0;
+    uint64_t key[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) key[c] = c < nc ? sw.keys[a.col0 + c] : 0;
     const uint32_t ntiles = (dim + kBlock - 1) / kBlock;
     for_each_tile(ntiles, local, sw.G, kXcdSuperShift, [&](uint32_t tile) {
         const uint32_t t = tile * kBlock + threadIdx.x;
         if (t >= dim) return;
-        const uint64_t i = t;
+        T* row = q + uint64_t(t) * a.block_ld + (a.col0 - a.block0);
+        T v[CB];
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
+            v[c] = T(0);
             if (c < nc) {
-                const uint32_t col = a.col0 + c;
-                const T v = T(start_entry(a.dist, sw.keys[col], i, sw.r0 + col));
-                q[uint64_t(t) * a.block_ld + (col - a.block0)] = v;
-                part[c] += double(v) * double(v);
+                v[c] = T(start_entry(a.dist, key[c], t, sw.r0 + a.col0 + c));
+                part[c] += double(v[c]) * double(v[c]);
             }
+        }
+        if (nc == CB) {
+            store_row<T, CB>(row, v);
+        } else {
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                if (c < nc) row[c] = v[c];
         }
     });
     block_sum<CB>(part, red, sw.partials + size_t(local) * a.ld + a.col0, nc);
@@ -504,7 +519,12 @@ __global__ void chain_init_kernel(LanczosLaunch a) {
 
 hipError_t launch_start(const LanczosLaunch& a, hipStream_t st) {
     const dim3 g(unsigned(a.grid)), b(kBlock);
-    if (a.vb < 1 || a.vb > 4) return hipErrorInvalidValue;
+    if (a.vb < 1 || a.vb > 8) return hipErrorInvalidValue;
+    if (a.vb > 4) {
+        if (a.dtype == 0) hipLaunchKernelGGL((start_kernel<float, 8>), g, b, 0, st, a);
+        else hipLaunchKernelGGL((start_kernel<double, 8>), g, b, 0, st, a);
+        return hipGetLastError();
+    }
     if (a.dtype == 0) hipLaunchKernelGGL((start_kernel<float, 4>), g, b, 0, st, a);
     else hipLaunchKernelGGL((start_kernel<double, 4>), g, b, 0, st, a);
     return hipGetLastError();

@@ -204,6 +204,17 @@ __device__ __forceinline__ void hv_body(const SectorDev& S, const BondTable& B, 
                 B, acc, anti};
             visit_row<L, MODE>(t, S.n_up, B, C, S.basis, table_map<MODE>(S), lds.ylds, vis);
             load_row<T, VB>(x + uint64_t(t) * ld + col0, xt);
+            if constexpr (EPI == kEpiPlain && MODE == kModeCr && VB <= 8) {
+                // the two slots weigh row 0 by zero for a bond that does not
+                // flip: an infinity or a NaN there makes the sum a NaN, and the
+                // row is walked once more, loading its own terms only
+                if (!all_finite<T, VB>(acc)) {
+#pragma unroll
+                    for (int c = 0; c < VB; ++c) acc[c] = T(0);
+                    anti = T(0);
+                    cr_bonds<L, false>(t, L(0), S.n_up, B, C, lds.ylds, vis);
+                }
+            }
             const T diag = jsum4 - anti;
 #pragma unroll
             for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];

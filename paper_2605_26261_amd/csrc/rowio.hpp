@@ -55,6 +55,15 @@ __device__ __forceinline__ void store_row(T* __restrict__ p, const T (&v)[VB]) {
     }
 }
 
+// No infinity and no NaN among VB values.
+template <typename T, int VB>
+__device__ __forceinline__ bool all_finite(const T (&v)[VB]) {
+    T z = T(0);
+#pragma unroll
+    for (int c = 0; c < VB; ++c) z += T(0) * v[c];
+    return z == T(0);
+}
+
 // Fourth word of a raw buffer resource on gfx9: data format 32 bits (a zero
 // format makes every load return 0), no stride, no swizzle.
 constexpr int kBufferWord3 = 0x00020000;

@@ -210,6 +210,17 @@ __device__ __forceinline__ void hv_spin_body(const SectorDev& S, const BondTable
                                                             uint32_t(ld * sizeof(T)), S.dim - 1, B, acc, diag};
             spin_row<MODE, T>(t, S, B, l, vis);
             load_row<T, VB>(x + uint64_t(t) * ld + col0, xt);
+            if constexpr (EPI == kEpiPlain && MODE == kModeCr) {
+                // as in hv_body: a row whose slots met an infinity or a NaN in
+                // row 0 is walked once more, loading its own terms only
+                if (!all_finite<T, VB>(acc)) {
+#pragma unroll
+                    for (int c = 0; c < VB; ++c) acc[c] = T(0);
+                    diag = T(0);
+                    spin_cr_row<T>(t, S.n_up, S.two_s, B, CumDim{l.table, S.bw, S.two_s + 1}, ladder_factors<T>(l),
+                                   l.yp, l.ym, vis);
+                }
+            }
 #pragma unroll
             for (int c = 0; c < VB; ++c) out[c] = diag * xt[c] + acc[c];
             T* yrow = y + uint64_t(r) * ld + col0;

@@ -36,3 +36,13 @@ def test_spin_half(n, n_up, mode, dtype):
     g, sec = ftlm.Graph(n, graphs.j1j2_ring(n)), ftlm.Sector(n, n_up, mode)
     for cols in (1, 2, 4, 8, 16):
         check(sec, g, cols, dtype)
+
+
+# 73,789 rows, and 19,611,175 (one and two columns by runs)
+@pytest.mark.parametrize("two_s,a", [(2, 12), (4, 24)])
+@pytest.mark.parametrize("mode", [ftlm.CR, ftlm.CLT])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_general_spin(two_s, a, mode, dtype):
+    g, sec = ftlm.Graph(12, graphs.ring(12)), ftlm.Sector(12, a, mode, two_s=two_s)
+    for cols in (1, 2, 4):
+        check(sec, g, cols, dtype)

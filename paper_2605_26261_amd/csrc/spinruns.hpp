@@ -199,7 +199,9 @@ struct SpinSlot {
 // lo + 64 + l, ...), as run_block. Bonds go in the sorted order of the bond
 // table, each with its terms e = +1 and -1, one bond a slot, two slots in turn:
 // every sum has the terms of spin_cr_row in the same order, with the same
-// weights. A row without a term loads nothing for it.
+// weights, each fused with its product (left to the compiler, a product that
+// ended in another block than its sum was rounded by itself: 3 % of the rows of
+// one column differed in the last bit). A row without a term loads nothing for it.
 template <typename T, int VB, int R>
 __device__ __forceinline__ void spin_run_block(const SectorDev& S, const BondTable& B, const uint16_t* rank,
                                                const SpinLow& L, const T* pairs, const SpinRun& run, SpinTerms<T>& st,
@@ -242,7 +244,7 @@ __device__ __forceinline__ void spin_run_block(const SectorDev& S, const BondTab
 #pragma unroll
             for (int i = 0; i < R; ++i)
 #pragma unroll
-                for (int k = 0; k < VB; ++k) acc[i][k] += sl.w[g][i] * sl.v[g][i][k];
+                for (int k = 0; k < VB; ++k) acc[i][k] = fma(sl.w[g][i], sl.v[g][i][k], acc[i][k]);
     };
 #pragma unroll
     for (int i = 0; i < R; ++i) dsum[i] = st.dsum;

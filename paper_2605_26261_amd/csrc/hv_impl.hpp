@@ -423,15 +423,15 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
 // evicted before their reuse (N = 30, 20 columns: 40.5 -> 38.9 ms; two
 // workgroups 44.9). Narrower blocks keep the register-limited occupancy (8
 // columns: 15.9 against 18.1 ms with the floor, 16: 31.3 against 33.6).
-// A block of up to 2^18 rows has no such choice of rows in flight.
+// A product of up to 2^18 rows has no such choice of rows in flight.
 template <typename T, int VB>
-size_t hv_plain_lds_floor(uint32_t dim) {
-    return (sizeof(T) == 4 && VB >= 20 && dim > (1u << 18)) ? size_t(48) * 1024 : 0;
+size_t hv_plain_lds_floor(uint32_t nrows) {
+    return (sizeof(T) == 4 && VB >= 20 && nrows > (1u << 18)) ? size_t(48) * 1024 : 0;
 }
 
 template <typename L, int MODE, typename T, int VB, bool BUF = false>
 hipError_t launch_hv_one(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
-    const size_t need = hv_lds_bytes(s), floor = hv_plain_lds_floor<T, VB>(s.dim);
+    const size_t need = hv_lds_bytes(s), floor = hv_plain_lds_floor<T, VB>(h.nrows);
     const size_t lds = need > floor ? need : floor;
     auto kern = hv_kernel<L, MODE, T, VB, BUF>;
     if (lds > 65536) {
@@ -522,7 +522,7 @@ inline double run_count(int n_sites, int n_up, int low_bits) {
     return runs;
 }
 
-// Whether a product of `row_bytes` a row goes by runs. Below about a million
+// Whether a product over all rows of a sector, `row_bytes` each, goes by runs. Below about a million
 // rows the row-by-row kernel's shorter start wins (N = 22, one FP32 vector: 30
 // against 40 us; N = 23: 55 against 49; N = 24: 110 against 79, and from 8- and
 // 16-byte rows on the lines lie one and two doublings higher). A run costs
@@ -549,6 +549,56 @@ inline bool by_runs(const SectorDev& s, size_t row_bytes) {
     if (row_bytes > 16) return false;
     if (s.n_sites > 32 && dim >= 67108864.0) return runs <= (row_bytes <= 8 ? 10.0 : 5.0) * unit;
     return row_bytes <= 8 && dim >= 12582912.0 && runs <= 4.0 * unit;
+}
+
+// Pascal's triangle for the host's counts (C(64, 32) < 2^63).
+struct Choose {
+    uint64_t c[kMaxSites + 1][kMaxSites + 1];
+    constexpr Choose() : c{} {
+        for (int n = 0; n <= kMaxSites; ++n) {
+            c[n][0] = 1;
+            for (int k = 1; k <= n; ++k) c[n][k] = c[n - 1][k - 1] + (k < n ? c[n - 1][k] : 0);
+        }
+    }
+};
+inline constexpr Choose kChoose{};
+
+// Runs that begin before the one of sector row `row`.
+inline uint64_t runs_before(int n_sites, int n_up, int low_bits, uint64_t row) {
+    uint64_t runs = 0;
+    int A = n_up;  // up spins among the sites 0 .. p
+    for (int p = n_sites - 1; p >= low_bits && A > 0; --p) {
+        const uint64_t rows = A <= p ? kChoose.c[p][A] : 0;  // with site p down
+        if (row < rows) continue;
+        const int nh = p - low_bits;
+        for (int a = A > low_bits ? A - low_bits : 0; a <= nh && a <= A; ++a) runs += kChoose.c[nh][a];
+        row -= rows;
+        --A;
+    }
+    return runs;
+}
+
+// Whether a product over a share of a sector's rows goes by runs: where one over
+// all rows does, if the share has enough rows and enough of them to a run. The
+// runs are counted, as a sector's first and last rows have many short ones. One
+// FP32 vector, microseconds by runs and row by row: N = 30, 2^16 rows 23 and 14,
+// 2^20 from the middle 55 and 62, from the end 117 and 62, 2^22 from the middle
+// 115 and 203, from the end 200 and 204; N = 34, 11 up, 64-bit labels, 2^20 from
+// the beginning 46 and 90, from the middle 199 and 90, 2^23 577 and 696. A row is
+// dearer with wider vectors or 64-bit labels, a run costs about the same.
+inline bool share_by_runs(const SectorDev& s, size_t row_bytes, uint32_t row0, uint32_t nrows) {
+    if (!by_runs(s, row_bytes)) return false;
+    if (nrows == s.dim) return true;
+    const int low = run_shape(row_bytes).low_bits;
+    const uint64_t runs = runs_before(s.n_sites, s.n_up, low, uint64_t(row0) + nrows - 1) -
+                          runs_before(s.n_sites, s.n_up, low, row0) + 1;
+    const bool table = s.mode == kModeClt || s.mode == kModeLin;
+    double least, per_run;  // rows
+    if (row_bytes <= 4) least = table ? 1.5 : 1.0, per_run = table ? 1200.0 : 700.0;
+    else if (row_bytes <= 8) least = table ? 1.0 : 1.25, per_run = table ? 650.0 : 500.0;
+    else least = row_bytes <= 16 ? 3.0 : 1.0, per_run = 250.0;
+    if (s.n_sites > 32) least *= 2.0, per_run *= 0.35;
+    return double(nrows) >= least * 1048576.0 + per_run * double(runs);
 }
 
 template <typename L, typename T, int VB>
@@ -580,8 +630,8 @@ hipError_t launch_hv_runs(const SectorDev& s, const BondTable& B, HvLaunch h, hi
 // = 26, 17 up, 8 columns: 308 against 271 us; N = 30: 22.4 against 15.9 ms) and
 // in place of the full table at any width (N = 26, 17 up, one column: 301
 // against 146 us).
-inline int product_map(const SectorDev& s, size_t row_bytes) {
-    const bool rank = s.dim >= (1u << 18) && (row_bytes > 8 || s.mode == kModeFull);
+inline int product_map(const SectorDev& s, size_t row_bytes, uint32_t nrows) {
+    const bool rank = nrows >= (1u << 18) && (row_bytes > 8 || s.mode == kModeFull);
     return rank ? kModeCr : s.mode;
 }
 
@@ -607,7 +657,7 @@ template <typename T>
 hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
     const size_t row_bytes = size_t(h0.vb) * sizeof(T);
     HvLaunch h = h0;
-    if (by_runs(s, row_bytes)) {
+    if (share_by_runs(s, row_bytes, h.row0, h.nrows)) {
         auto go = [&](auto vb) {
             constexpr int VB = decltype(vb)::value;
             return s.n_sites > 32 ? launch_hv_runs<uint64_t, T, VB>(s, B, h, st)
@@ -621,7 +671,7 @@ hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunc
     }
     h.grid = int(hv_grid(h.nrows, row_bytes));
     h.super_shift = plain_super_shift((uint64_t(h.nrows) + kBlock - 1) / kBlock, row_bytes <= 16 ? 4 : 6);
-    const int mode = product_map(s, row_bytes);
+    const int mode = product_map(s, row_bytes, h.nrows);
     const bool buf = h.vb == 1 && h.ld == 1 && h.col0 == 0 && uint64_t(s.dim) * sizeof(T) < (uint64_t(1) << 32) &&
                      (mode == kModeCr || mode == kModeClt);
     SectorDev sm = s;

@@ -527,11 +527,13 @@ __global__ __launch_bounds__(kBlock) void neighbors_spin_kernel(SectorDev S, Bon
 // by runs), from 2^23 of them (s = 3/2, 1.7 million: 104 against 111 us), at least
 // 192 to a run on average. Icosahedron, FP32, one column: s = 2, M = 0 with 260 a
 // run 1100 -> 838 us, M = 6 with 130 564 against 764; s = 5/2, M = 8 with 220 3484
-// -> 2288, M = 12 with 85 1442 -> 1299 (with the compressed table 925).
-static bool spin_by_runs(const SectorDev& s, size_t row_bytes, uint64_t ldb) {
+// -> 2288, M = 12 with 85 1442 -> 1299 (with the compressed table 925). A share
+// of the rows needs 2^31 / (rows to a run) of them: s = 2, M = 0, 2^16 rows 43
+// against 16 us row by row, 2^22 265 against 242, 2^23 393 against 477; s = 5/2 with
+// 517 a run 2^16 60 against 17, 2^22 221 against 251.
+static bool spin_by_runs(const SectorDev& s, size_t row_bytes, uint32_t nrows) {
     const int d = s.two_s + 1, low = spin_low_sites(d), nh = s.n_sites - low;
     if (d > 6 || nh <= 0 || row_bytes > 8 || s.dim < (1u << 23)) return false;
-    if (ldb > (uint64_t(1) << 19)) return false;  // a run's rows lie within 2^31 bytes
     // high patterns that leave the low sites a digit sum they can have
     double count[kMaxSpinSites * kMaxTwoS + 1] = {1.0};
     for (int q = 0; q < nh; ++q) {
@@ -546,6 +548,7 @@ static bool spin_by_runs(const SectorDev& s, size_t row_bytes, uint64_t ldb) {
     double runs = 0.0;
     for (int k = 0; k <= nh * s.two_s && k <= s.n_up; ++k)
         if (s.n_up - k <= low * s.two_s) runs += count[k];
+    if (nrows != s.dim && double(nrows) * double(s.dim) < 2147483648.0 * runs) return false;
     return double(s.dim) >= 192.0 * runs;
 }
 
@@ -570,7 +573,7 @@ hipError_t launch_hv_spin_runs(const SectorDev& s, const BondTable& B, HvLaunch 
 hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
     HvLaunch h = h0;
     const size_t row_bytes = size_t(h.vb) * (h.dtype == 0 ? 4 : 8);
-    if (spin_by_runs(s, row_bytes, h.ld * (h.dtype == 0 ? 4 : 8))) {
+    if (spin_by_runs(s, row_bytes, h.nrows)) {
         if (h.dtype != 0) return launch_hv_spin_runs<double, 1>(s, B, h, st);
         return h.vb == 1 ? launch_hv_spin_runs<float, 1>(s, B, h, st) : launch_hv_spin_runs<float, 2>(s, B, h, st);
     }

@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void hv_kernel(SectorDev S, BondTable B, Hv
 // 16-byte rows 7.3 (12 and 14 sites 7.5; one row a lane 8.1), 32-byte rows
 // 14.4 (12 sites, 64 rows a wave; 128 rows 15.2). Narrow rows spread over 8192
 // blocks, whose rank tables are staged once for several tiles; for wider ones
-// a block takes one tile, see hv_grid.
+// a block takes one tile, see walk_schedule.
 struct RunShape {
     int lane_rows, low_bits;
     uint32_t chunk, blocks;
@@ -505,9 +505,9 @@ hipError_t with_mode(int mode, int n_sites, F&& f) {
 // 256; N = 30 within 0.3 %) or 16 (2^most), fewer where an XCD would get less
 // than 16 super-tiles (16 sites, 51 tiles: super-tiles of 16 went to four of the
 // XCDs and took 22 us, single tiles take 9).
-inline int plain_super_shift(uint64_t ntiles, int most) {
+inline int plain_super_shift(uint64_t ntiles, int most, uint64_t least_supers = 128) {
     int s = most;
-    while (s > 0 && (ntiles >> s) < 128) --s;
+    while (s > 0 && (ntiles >> s) < least_supers) --s;
     return s;
 }
 
@@ -635,16 +635,32 @@ inline int product_map(const SectorDev& s, size_t row_bytes, uint32_t nrows) {
     return rank ? kModeCr : s.mode;
 }
 
-// Blocks of the row-by-row kernel. Rows of up to 16 bytes: a persistent grid of
-// at most 2048 (latency-bound; one block per tile, whose tables are staged each
-// time, gave 8.0 against 7.4 ms at one column). Wider rows are bound by the
-// lines they miss in L2, and a block takes one tile: blocks are dispatched in
-// order, so the rows in flight stay one compact front, where the blocks of a
-// persistent grid drift apart and share fewer partner rows. N = 30, FP32: 8
-// columns 17.7 -> 15.9 ms, 12 28.9 -> 23.7, 16 42.0 -> 31.2, 20 55.4 -> 38.9,
-// 4 FP64 columns 19.5 -> 14.8.
-inline uint32_t hv_grid(uint32_t nrows, size_t row_bytes) {
-    return row_bytes <= 16 ? rows_grid(nrows) : capped_grid(nrows, 1u << 30);
+// Blocks of the row-by-row kernel and its super-tiles. Rows of up to 16 bytes: a
+// persistent grid of at most 2048 (latency-bound; one block per tile, whose tables
+// are staged each time, gave 8.0 against 7.4 ms at one column). Wider rows are
+// bound by the lines they miss in L2, and a block takes one tile: blocks are
+// dispatched in order, so the rows in flight stay one compact front, where the
+// blocks of a persistent grid drift apart and share fewer partner rows. N = 30,
+// FP32: 8 columns 17.7 -> 15.9 ms, 12 28.9 -> 23.7, 16 42.0 -> 31.2, 20 55.4 ->
+// 38.9, 4 FP64 columns 19.5 -> 14.8.
+// Up to `few_tiles` most blocks of a persistent grid take one tile or a few and
+// have no time to drift: it saves the staging, and eight super-tiles to an XCD do,
+// of up to 32 tiles (kFewTiles, for FP32 rows of up to 80 bytes, spin 1/2, twice as
+// many: FP64 blocks of 4 columns 80.7 and 81.7 at 5282 tiles, s = 3/2, 16 FP32
+// columns 2 x 8 10 % longer at 6640). Microseconds,
+// one tile a block (super-tiles as for large sectors) and this: 1378 tiles, 8, 16
+// and 20 FP32 columns 30.0, 63.9, 66.2 and 28.1, 60.4, 61.7; 2755 tiles, 8, 10, 16
+// and 32 54.0, 87.7, 122.6, 275 and 49.9, 77.9, 113.9, 262; 5282 tiles, 8, 10, 20
+// and 32 87.8, 136.7, 251.8, 471 and 84.7, 129.2, 228.4, 499; 10,564 tiles, 8
+// columns 178 and 198.
+constexpr uint32_t kFewTiles = 4096;
+inline void walk_schedule(uint32_t nrows, size_t row_bytes, uint32_t few_tiles, HvLaunch& h) {
+    const uint64_t ntiles = (uint64_t(nrows) + kBlock - 1) / kBlock;
+    const bool narrow = row_bytes <= 16, few = ntiles < few_tiles;
+    h.grid = int(narrow || few ? rows_grid(nrows) : capped_grid(nrows, 1u << 30));
+    h.super_shift = narrow ? plain_super_shift(ntiles, 4)
+                    : few ? plain_super_shift(ntiles, 5, ntiles < 1024 ? 128 : 64)
+                          : plain_super_shift(ntiles, 6);
 }
 
 // A single contiguous vector of fewer than 2^32 bytes takes the
@@ -669,8 +685,7 @@ hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunc
         if constexpr (sizeof(T) == 4)
             if (h.vb == 8) return go(std::integral_constant<int, 8>{});
     }
-    h.grid = int(hv_grid(h.nrows, row_bytes));
-    h.super_shift = plain_super_shift((uint64_t(h.nrows) + kBlock - 1) / kBlock, row_bytes <= 16 ? 4 : 6);
+    walk_schedule(h.nrows, row_bytes, sizeof(T) == 4 && row_bytes <= 80 ? 2 * kFewTiles : kFewTiles, h);
     const int mode = product_map(s, row_bytes, h.nrows);
     const bool buf = h.vb == 1 && h.ld == 1 && h.col0 == 0 && uint64_t(s.dim) * sizeof(T) < (uint64_t(1) << 32) &&
                      (mode == kModeCr || mode == kModeClt);

@@ -577,8 +577,7 @@ hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch
         if (h.dtype != 0) return launch_hv_spin_runs<double, 1>(s, B, h, st);
         return h.vb == 1 ? launch_hv_spin_runs<float, 1>(s, B, h, st) : launch_hv_spin_runs<float, 2>(s, B, h, st);
     }
-    h.grid = int(hv_grid(h.nrows, row_bytes));
-    h.super_shift = plain_super_shift((uint64_t(h.nrows) + kBlock - 1) / kBlock, row_bytes <= 16 ? 4 : 6);
+    walk_schedule(h.nrows, row_bytes, kFewTiles, h);
     const size_t lds = hv_spin_lds_bytes(s);
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);

@@ -522,10 +522,13 @@ inline double run_count(int n_sites, int n_up, int low_bits) {
     return runs;
 }
 
-// Whether a product over all rows of a sector, `row_bytes` each, goes by runs. Below about a million
-// rows the row-by-row kernel's shorter start wins (N = 22, one FP32 vector: 30
-// against 40 us; N = 23: 55 against 49; N = 24: 110 against 79, and from 8- and
-// 16-byte rows on the lines lie one and two doublings higher). A run costs
+// Whether a product over all rows of a sector, `row_bytes` each, goes by runs.
+// Below about a million rows the row-by-row kernel's shorter start wins (N = 22,
+// one FP32 vector: 30 against 40 us; N = 23: 55 against 49; N = 24: 110 against 79;
+// 8-byte rows a doubling higher). 16-byte rows have the line at `least16` million
+// of them: 32 for FP32 products (20.1 M rows 1029 us row by row, 1064 by runs; 40.1
+// M 1990 and 1840), 8 for FP64 ones (5.2 M 217 and 224; 10.4 M 542 and 509), 4 for
+// the Lanczos step of FP32 vectors (10.4 M, with its update, 717 and 637). A run costs
 // about two passes of a wave whatever its length, so there must be rows to
 // each: sectors near half filling have 400 runs per million rows with 14 low
 // sites and twice as many per site less. With three times as many, 13 million
@@ -535,13 +538,13 @@ inline double run_count(int n_sites, int n_up, int low_bits) {
 // 10.7 -> 7.2 ms). 32-byte rows are bound by the lines they miss either way
 // and gain only in the largest sectors (N = 30: 15.9 -> 14.4 ms, N = 28 equal);
 // wider rows do not (16 FP32 columns: 31.2 against 32.2 ms).
-inline bool by_runs(const SectorDev& s, size_t row_bytes) {
+inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16) {
     if (row_bytes > 32) return false;
     const RunShape shape = run_shape(row_bytes);
     if (s.n_sites <= shape.low_bits) return false;
     const bool table = s.mode == kModeClt || s.mode == kModeLin;
     const double dim = double(s.dim);
-    const double least = row_bytes <= 4 ? (table ? 4.0 : 1.25) : row_bytes <= 8 ? 2.0 : row_bytes <= 16 ? 4.0 : 64.0;
+    const double least = row_bytes <= 4 ? (table ? 4.0 : 1.25) : row_bytes <= 8 ? 2.0 : row_bytes <= 16 ? least16 : 64.0;
     if (dim < least * 1048576.0) return false;
     const double unit = double(1u << (14 - shape.low_bits)) * 500e-6 * dim;  // 500 per million rows at 14 sites
     const double runs = run_count(s.n_sites, s.n_up, shape.low_bits);
@@ -586,8 +589,8 @@ inline uint64_t runs_before(int n_sites, int n_up, int low_bits, uint64_t row) {
 // 115 and 203, from the end 200 and 204; N = 34, 11 up, 64-bit labels, 2^20 from
 // the beginning 46 and 90, from the middle 199 and 90, 2^23 577 and 696. A row is
 // dearer with wider vectors or 64-bit labels, a run costs about the same.
-inline bool share_by_runs(const SectorDev& s, size_t row_bytes, uint32_t row0, uint32_t nrows) {
-    if (!by_runs(s, row_bytes)) return false;
+inline bool share_by_runs(const SectorDev& s, size_t row_bytes, bool f64, uint32_t row0, uint32_t nrows) {
+    if (!by_runs(s, row_bytes, f64 ? 8.0 : 32.0)) return false;
     if (nrows == s.dim) return true;
     const int low = run_shape(row_bytes).low_bits;
     const uint64_t runs = runs_before(s.n_sites, s.n_up, low, uint64_t(row0) + nrows - 1) -
@@ -673,7 +676,7 @@ template <typename T>
 hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
     const size_t row_bytes = size_t(h0.vb) * sizeof(T);
     HvLaunch h = h0;
-    if (share_by_runs(s, row_bytes, h.row0, h.nrows)) {
+    if (share_by_runs(s, row_bytes, sizeof(T) == 8, h.row0, h.nrows)) {
         auto go = [&](auto vb) {
             constexpr int VB = decltype(vb)::value;
             return s.n_sites > 32 ? launch_hv_runs<uint64_t, T, VB>(s, B, h, st)

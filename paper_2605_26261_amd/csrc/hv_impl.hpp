@@ -632,9 +632,11 @@ hipError_t launch_hv_runs(const SectorDev& s, const BondTable& B, HvLaunch h, hi
 // rows on for wider rows, where the table's loads come on top of the rows' (N
 // = 26, 17 up, 8 columns: 308 against 271 us; N = 30: 22.4 against 15.9 ms) and
 // in place of the full table at any width (N = 26, 17 up, one column: 301
-// against 146 us).
-inline int product_map(const SectorDev& s, size_t row_bytes, uint32_t nrows) {
-    const bool rank = nrows >= (1u << 18) && (row_bytes > 8 || s.mode == kModeFull);
+// against 146 us). 16 FP64 columns keep the map at any size: the ranking takes
+// such rows bond by bond, the maps two at a time (N = 24: table 1034, ranking 1250
+// us; N = 27 9.7 and 12.4 ms).
+inline int product_map(const SectorDev& s, size_t row_bytes, bool f64, uint32_t nrows) {
+    const bool rank = nrows >= (1u << 18) && (row_bytes > 8 || s.mode == kModeFull) && !(f64 && row_bytes >= 128);
     return rank ? kModeCr : s.mode;
 }
 
@@ -689,7 +691,7 @@ hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunc
             if (h.vb == 8) return go(std::integral_constant<int, 8>{});
     }
     walk_schedule(h.nrows, row_bytes, sizeof(T) == 4 && row_bytes <= 80 ? 2 * kFewTiles : kFewTiles, h);
-    const int mode = product_map(s, row_bytes, h.nrows);
+    const int mode = product_map(s, row_bytes, sizeof(T) == 8, h.nrows);
     const bool buf = h.vb == 1 && h.ld == 1 && h.col0 == 0 && uint64_t(s.dim) * sizeof(T) < (uint64_t(1) << 32) &&
                      (mode == kModeCr || mode == kModeClt);
     SectorDev sm = s;

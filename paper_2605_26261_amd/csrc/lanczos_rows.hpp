@@ -265,7 +265,7 @@ inline int lanczos_path(LanczosLaunch& a) {
         a.xcd_items = int(xcd_items((slots + (1u << a.item_log) - 1u) >> a.item_log, 0));
         return kPathRuns;
     }
-    const int mode = product_map(s, row_bytes, s.dim);
+    const int mode = product_map(s, row_bytes, false, s.dim);
     return a.vb > 8 ? kModeCr : mode;
 }
 

@@ -423,15 +423,23 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
 // evicted before their reuse (N = 30, 20 columns: 40.5 -> 38.9 ms; two
 // workgroups 44.9). Narrower blocks keep the register-limited occupancy (8
 // columns: 15.9 against 18.1 ms with the floor, 16: 31.3 against 33.6).
-// A product of up to 2^18 rows has no such choice of rows in flight.
+// A product of 32 columns over up to 2^18 rows has no such choice of rows in
+// flight (184,756 rows: 78.9 us without a floor, 82.2 with two workgroups, but 20
+// columns 44.9 and 42.9). Rows of more than 32 columns that are not whole lines
+// take several launches, each of which fetches lines of its neighbours: two
+// workgroups (52 columns, 705,432 rows 666 us with three, 609 with two; 64 columns
+// 526 and 565).
 template <typename T, int VB>
-size_t hv_plain_lds_floor(uint32_t nrows) {
-    return (sizeof(T) == 4 && VB >= 20 && nrows > (1u << 18)) ? size_t(48) * 1024 : 0;
+size_t hv_plain_lds_floor(const HvLaunch& h) {
+    if (sizeof(T) != 4 || VB < 20) return 0;
+    const bool lines = h.ld % 32 == 0, few = h.nrows <= (1u << 18);
+    if (!lines && (h.ld > 32 || few)) return size_t(72) * 1024;
+    return few ? 0 : size_t(48) * 1024;
 }
 
 template <typename L, int MODE, typename T, int VB, bool BUF = false>
 hipError_t launch_hv_one(const SectorDev& s, const BondTable& B, const HvLaunch& h, hipStream_t st) {
-    const size_t need = hv_lds_bytes(s), floor = hv_plain_lds_floor<T, VB>(h.nrows);
+    const size_t need = hv_lds_bytes(s), floor = hv_plain_lds_floor<T, VB>(h);
     const size_t lds = need > floor ? need : floor;
     auto kern = hv_kernel<L, MODE, T, VB, BUF>;
     if (lds > 65536) {

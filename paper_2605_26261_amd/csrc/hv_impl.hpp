@@ -540,13 +540,15 @@ inline double run_count(int n_sites, int n_up, int low_bits) {
 // about two passes of a wave whatever its length, so there must be rows to
 // each: sectors near half filling have 400 runs per million rows with 14 low
 // sites and twice as many per site less. With three times as many, 13 million
-// rows still gain (28 sites, 18 up, 8-byte rows 558 -> 532 us), 3 million lose
-// (26 sites, 17 up: 156 -> 290 us); above 32 sites, where the row-by-row
+// rows still gain (28 sites, 18 up, 8-byte rows 558 -> 532 us), but not one FP32
+// vector of a sector with a table (345 -> 441; the third of three, whose lines are
+// wider, does: 1134 -> 991 in all), and 3 million lose (26 sites, 17 up: 156
+// -> 290 us); above 32 sites, where the row-by-row
 // kernel walks 64-bit labels, ten times as many still pay (34 sites, 10 up:
 // 10.7 -> 7.2 ms). 32-byte rows are bound by the lines they miss either way
 // and gain only in the largest sectors (N = 30: 15.9 -> 14.4 ms, N = 28 equal);
 // wider rows do not (16 FP32 columns: 31.2 against 32.2 ms).
-inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16) {
+inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16, bool part = false) {
     if (row_bytes > 32) return false;
     const RunShape shape = run_shape(row_bytes);
     if (s.n_sites <= shape.low_bits) return false;
@@ -559,7 +561,7 @@ inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16) {
     if (runs <= unit) return true;
     if (row_bytes > 16) return false;
     if (s.n_sites > 32 && dim >= 67108864.0) return runs <= (row_bytes <= 8 ? 10.0 : 5.0) * unit;
-    return row_bytes <= 8 && dim >= 12582912.0 && runs <= 4.0 * unit;
+    return row_bytes <= 8 && dim >= 12582912.0 && runs <= (table && row_bytes <= 4 && !part ? 2.0 : 4.0) * unit;
 }
 
 // Pascal's triangle for the host's counts (C(64, 32) < 2^63).
@@ -597,8 +599,9 @@ inline uint64_t runs_before(int n_sites, int n_up, int low_bits, uint64_t row) {
 // 115 and 203, from the end 200 and 204; N = 34, 11 up, 64-bit labels, 2^20 from
 // the beginning 46 and 90, from the middle 199 and 90, 2^23 577 and 696. A row is
 // dearer with wider vectors or 64-bit labels, a run costs about the same.
-inline bool share_by_runs(const SectorDev& s, size_t row_bytes, bool f64, uint32_t row0, uint32_t nrows) {
-    if (!by_runs(s, row_bytes, f64 ? 8.0 : 32.0)) return false;
+inline bool share_by_runs(const SectorDev& s, size_t row_bytes, bool f64, const HvLaunch& h) {
+    const uint32_t row0 = h.row0, nrows = h.nrows;
+    if (!by_runs(s, row_bytes, f64 ? 8.0 : 32.0, h.ld > uint64_t(h.vb))) return false;
     if (nrows == s.dim) return true;
     const int low = run_shape(row_bytes).low_bits;
     const uint64_t runs = runs_before(s.n_sites, s.n_up, low, uint64_t(row0) + nrows - 1) -
@@ -686,7 +689,7 @@ template <typename T>
 hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
     const size_t row_bytes = size_t(h0.vb) * sizeof(T);
     HvLaunch h = h0;
-    if (share_by_runs(s, row_bytes, sizeof(T) == 8, h.row0, h.nrows)) {
+    if (share_by_runs(s, row_bytes, sizeof(T) == 8, h)) {
         auto go = [&](auto vb) {
             constexpr int VB = decltype(vb)::value;
             return s.n_sites > 32 ? launch_hv_runs<uint64_t, T, VB>(s, B, h, st)

@@ -429,12 +429,14 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
 // take several launches, each of which fetches lines of its neighbours: two
 // workgroups (52 columns, 705,432 rows 666 us with three, 609 with two; 64 columns
 // 526 and 565).
+inline bool two_to_a_cu(const HvLaunch& h) {
+    return h.dtype == 0 && h.vb >= 20 && h.ld % 32 != 0 && (h.ld > 32 || h.nrows <= (1u << 18));
+}
 template <typename T, int VB>
 size_t hv_plain_lds_floor(const HvLaunch& h) {
     if (sizeof(T) != 4 || VB < 20) return 0;
-    const bool lines = h.ld % 32 == 0, few = h.nrows <= (1u << 18);
-    if (!lines && (h.ld > 32 || few)) return size_t(72) * 1024;
-    return few ? 0 : size_t(48) * 1024;
+    if (two_to_a_cu(h)) return size_t(72) * 1024;
+    return h.nrows <= (1u << 18) ? 0 : size_t(48) * 1024;
 }
 
 template <typename L, int MODE, typename T, int VB, bool BUF = false>
@@ -510,12 +512,24 @@ hipError_t with_mode(int mode, int n_sites, F&& f) {
 
 // Tiles per XCD super-tile (log2) of a plain H.x over `ntiles` tiles: 64 tiles
 // (24-site square lattice, 8 columns: 363 us with 16, 342 with 64, 375 with
-// 256; N = 30 within 0.3 %) or 16 (2^most), fewer where an XCD would get less
-// than 16 super-tiles (16 sites, 51 tiles: super-tiles of 16 went to four of the
-// XCDs and took 22 us, single tiles take 9).
-inline int plain_super_shift(uint64_t ntiles, int most, uint64_t least_supers = 128) {
+// 256; N = 30 within 0.3 %) or 2^most, fewer where there would be less than
+// `least` super-tiles.
+inline int plain_super_shift(uint64_t ntiles, int most, uint64_t least = 128) {
     int s = most;
-    while (s > 0 && (ntiles >> s) < least_supers) --s;
+    while (s > 0 && (ntiles >> s) < least) --s;
+    return s;
+}
+
+// The same for a grid with a block for every tile: the largest with which no
+// block of an XCD takes a second tile while another has none (692 tiles, one FP32
+// column: 12.1 us with single tiles, 19.7 with 2, 4, 8 or 16).
+inline int single_tile_shift(uint64_t ntiles, int most) {
+    int s = most;
+    for (; s > 0; --s) {
+        const uint64_t full = ntiles >> s, part = ntiles & ((uint64_t(1) << s) - 1);
+        const uint64_t xcd0 = full % 8 ? (full / 8 + 1) << s : (full / 8 << s) + part;
+        if (xcd0 <= (ntiles + 7) / 8) break;
+    }
     return s;
 }
 
@@ -660,23 +674,44 @@ inline int product_map(const SectorDev& s, size_t row_bytes, bool f64, uint32_t 
 // FP32: 8 columns 17.7 -> 15.9 ms, 12 28.9 -> 23.7, 16 42.0 -> 31.2, 20 55.4 ->
 // 38.9, 4 FP64 columns 19.5 -> 14.8.
 // Up to `few_tiles` most blocks of a persistent grid take one tile or a few and
-// have no time to drift: it saves the staging, and eight super-tiles to an XCD do,
-// of up to 32 tiles (kFewTiles, for FP32 rows of up to 80 bytes, spin 1/2, twice as
-// many: FP64 blocks of 4 columns 80.7 and 81.7 at 5282 tiles, s = 3/2, 16 FP32
-// columns 2 x 8 10 % longer at 6640). Microseconds,
-// one tile a block (super-tiles as for large sectors) and this: 1378 tiles, 8, 16
-// and 20 FP32 columns 30.0, 63.9, 66.2 and 28.1, 60.4, 61.7; 2755 tiles, 8, 10, 16
-// and 32 54.0, 87.7, 122.6, 275 and 49.9, 77.9, 113.9, 262; 5282 tiles, 8, 10, 20
-// and 32 87.8, 136.7, 251.8, 471 and 84.7, 129.2, 228.4, 499; 10,564 tiles, 8
-// columns 178 and 198.
-constexpr uint32_t kFewTiles = 4096;
-inline void walk_schedule(uint32_t nrows, size_t row_bytes, uint32_t few_tiles, HvLaunch& h) {
-    const uint64_t ntiles = (uint64_t(nrows) + kBlock - 1) / kBlock;
-    const bool narrow = row_bytes <= 16, few = ntiles < few_tiles;
-    h.grid = int(narrow || few ? rows_grid(nrows) : capped_grid(nrows, 1u << 30));
-    h.super_shift = narrow ? plain_super_shift(ntiles, 4)
-                    : few ? plain_super_shift(ntiles, 5, ntiles < 1024 ? 128 : 64)
-                          : plain_super_shift(ntiles, 6);
+// have no time to drift: it saves the staging. While the latency of a tile bounds
+// them, no block takes two tiles (single_tile_shift): up to 1280 tiles, 2048 for
+// narrow rows whose partners come from a table, 512 for rows that are a part of a
+// wider one and with two workgroups to a CU, which wait for lines (1378 tiles, one
+// FP32 column, table 11.5 us with single tiles, 14.0 with 8, ranking 18.3 with
+// either; 722 tiles, 52 columns 177 and 151). Beyond, eight super-tiles to an XCD do,
+// of up to 32 tiles. Microseconds, one tile a block (super-tiles as for large
+// sectors) and this: 1378 tiles, 8, 16 and 20 FP32 columns 30.0, 63.9, 66.2 and
+// 28.1, 60.4, 61.7; 2755 tiles, 8, 10, 16 and 32 54.0, 87.7, 122.6, 275 and 49.9,
+// 77.9, 113.9, 262; 10,564 tiles, 8 columns 178 and 198.
+inline void walk_schedule(size_t row_bytes, uint32_t few_tiles, bool table, HvLaunch& h) {
+    const uint64_t ntiles = (uint64_t(h.nrows) + kBlock - 1) / kBlock;
+    const bool narrow = row_bytes <= 16;
+    if (!narrow && ntiles >= few_tiles) {
+        h.grid = int(capped_grid(h.nrows, 1u << 30));
+        h.super_shift = plain_super_shift(ntiles, 6);
+        return;
+    }
+    const uint64_t stride = h.ld * (h.dtype == 0 ? 4 : 8);
+    const bool part = (stride > row_bytes && stride > 64) || two_to_a_cu(h);
+    h.grid = int(rows_grid(h.nrows));
+    h.super_shift = ntiles <= (part ? 512 : narrow && table ? 2048 : 1280) ? single_tile_shift(ntiles, 4)
+                    : part && ntiles <= 1024                               ? plain_super_shift(ntiles, 4, 40)
+                    : narrow ? plain_super_shift(ntiles, 4, part ? 64 : 128)
+                             : plain_super_shift(ntiles, 5, 64);
+}
+
+// Tiles from which on wide rows take one tile a block. FP32 rows of up to 80 bytes
+// and 64-bit labels: 8192 (5282 tiles, 8, 10 and 20 FP32 columns 87.8, 136.7 and
+// 251.8 us one tile a block, 84.7, 129.2 and 228.4 on the persistent grid; 48 sites,
+// 6689 tiles, 4 FP64 columns 300 and 284); else 4096 (32 FP32 columns 471 and 499,
+// 4 FP64 columns 80.7 and 81.7). FP32 rows of up to 40 bytes in sectors with few up,
+// or down, spins, which miss fewer lines: 16384 (28 sites, 20 up, 12,142 tiles, 8
+// columns 237 and 213).
+inline bool few_flips(int n_up, int most) { return 20 * (n_up < most - n_up ? n_up : most - n_up) < 7 * most; }
+inline uint32_t few_tiles(const SectorDev& s, size_t row_bytes, bool f32) {
+    if (f32 && row_bytes <= 40 && few_flips(s.n_up, s.n_sites)) return 16384;
+    return s.n_sites > 32 || (f32 && row_bytes <= 80) ? 8192 : 4096;
 }
 
 // A single contiguous vector of fewer than 2^32 bytes takes the
@@ -701,8 +736,8 @@ hipError_t launch_hv_typed(const SectorDev& s, const BondTable& B, const HvLaunc
         if constexpr (sizeof(T) == 4)
             if (h.vb == 8) return go(std::integral_constant<int, 8>{});
     }
-    walk_schedule(h.nrows, row_bytes, sizeof(T) == 4 && row_bytes <= 80 ? 2 * kFewTiles : kFewTiles, h);
     const int mode = product_map(s, row_bytes, sizeof(T) == 8, h.nrows);
+    walk_schedule(row_bytes, few_tiles(s, row_bytes, sizeof(T) == 4), mode != kModeCr, h);
     const bool buf = h.vb == 1 && h.ld == 1 && h.col0 == 0 && uint64_t(s.dim) * sizeof(T) < (uint64_t(1) << 32) &&
                      (mode == kModeCr || mode == kModeClt);
     SectorDev sm = s;

@@ -577,7 +577,12 @@ hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch
         if (h.dtype != 0) return launch_hv_spin_runs<double, 1>(s, B, h, st);
         return h.vb == 1 ? launch_hv_spin_runs<float, 1>(s, B, h, st) : launch_hv_spin_runs<float, 2>(s, B, h, st);
     }
-    walk_schedule(h.nrows, row_bytes, kFewTiles, h);
+    // one tile a block from 4096 tiles on; ranked, with few terms, from 16384 (s = 5/2, M =
+    // 16, 13,889 tiles, 8 FP32 columns 384 us one tile a block, 331 on the persistent
+    // grid, but 418 and 517 with the table; s = 2, M = 6, 37,313 tiles 802 and 934)
+    const bool whole = h.ld == uint64_t(h.vb);
+    const bool few = s.mode == kModeCr && row_bytes <= 32 && whole && few_flips(s.n_up, s.n_sites * s.two_s);
+    walk_schedule(row_bytes, few ? 16384 : 4096, s.mode != kModeCr, h);
     const size_t lds = hv_spin_lds_bytes(s);
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);

@@ -283,7 +283,10 @@ int ftlm_lanczos_noalloc(const ftlm_sector* s, const ftlm_graph* g, uint64_t see
  * scratch. It returns the B that minimizes the time of one Lanczos step of
  * all R chains run as floor(R / B) batches of B and one of R mod B, each
  * batch priced as the sum of its column chunks (the launch widths
- * ftlm_lanczos cuts it into). Results are cached per (N, n_up,
+ * ftlm_lanczos cuts it into). All chains of a sector of at most 1792 states run
+ * side by side in one launch: there whole runs of at most 32 steps are timed, R
+ * is a candidate as well, and a batch costs what the next larger candidate
+ * does. Results are cached per (N, n_up,
  * bonds, mode, dtype, R) for the life of the process; the file named by the
  * environment variable FTLM_AUTOTUNE_CACHE, when set, is read and appended
  * (one "key batch ms" line per entry). The workgroup grid is not tuned: it
@@ -341,9 +344,10 @@ int ftlm_plan_run(ftlm_plan* p, uint64_t seed, uint64_t r0, int dist, int use_gr
  * 16, 10, 8 and 4 columns (FP64: 16, 8, 4), distinct ones only; each is timed
  * over one Lanczos step of the whole plan, after a warm-up step, with HIP
  * events on the plan's stream (ordered after the work on `stream`), twice,
- * keeping the faster time. The fastest candidate is kept for later
- * ftlm_plan_run calls; a graph captured before is dropped and captured again
- * by the next run with use_graph != 0. Chains are bitwise the same under
+ * keeping the faster time (a plan whose sectors all have at most 1792 states
+ * runs in one launch under every split: its whole run is timed). The fastest
+ * candidate is kept for later ftlm_plan_run calls; a graph captured before is
+ * dropped and captured again by the next run with use_graph != 0. Chains are bitwise the same under
  * every split (the reduction order depends only on each sector's D). The
  * plan's vector blocks are overwritten. out may be NULL. Synchronizes.
  * Errors: FTLM_E_INVALID for a null plan, FTLM_E_DEVICE for a HIP error (the

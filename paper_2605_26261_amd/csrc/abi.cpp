@@ -463,12 +463,15 @@ struct TuneCache {
     std::map<std::string, std::pair<int, double>> entries;
 } g_tune;
 
-// "_c4": the candidate set, cost model and kernel set; a cache file written
+// Steps of the timed runs of tiny sectors, at most.
+constexpr int kTuneSteps = 32;
+
+// "_c5": the candidate set, cost model and kernel set; a cache file written
 // under an older one is not reused.
 std::string tune_key(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype) {
     std::string k = "N" + std::to_string(s->n_sites) + "_s" + std::to_string(s->two_s) + "_u" +
                     std::to_string(s->n_up) + "_m" + std::to_string(s->mode) + "_t" + std::to_string(dtype) + "_R" +
-                    std::to_string(R) + "_c4_b";
+                    std::to_string(R) + "_c5_b";
     // the bond structure, so that two graphs with the same size do not share entries
     uint64_t h = 1469598103934665603ull;
     for (size_t b = 0; b < g->bi.size(); ++b) {
@@ -524,43 +527,63 @@ int ftlm_autotune(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype, v
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     // every width a Lanczos launch can take (FP32 only: 10, 12, 20, 32), so
-    // that a batch of any size is priced from launches that were measured
-    const int widths[] = {1, 2, 4, 8, 10, 12, 16, 20, 32};
+    // that a batch of any size is priced from launches that were measured; all
+    // chains of a tiny sector also go in one launch
+    std::vector<int> widths = {1, 2, 4, 8, 10, 12, 16, 20, 32};
     const int widest = max_launch_width(s->two_s);
+    LanczosJob whole;
+    single_job(whole, s, g, R, 1, dtype, work_dev);
+    const bool tiny = by_tiny_chains(whole.launch());
+    widths.erase(std::remove_if(widths.begin(), widths.end(),
+                                [&](int B) {
+                                    return B > R || B > widest ||
+                                           (dtype == FTLM_F64 && (B > 16 || B == 10 || B == 12));
+                                }),
+                 widths.end());
+    if (tiny && widths.back() != R) widths.push_back(R);
     EventPair ev;
     HIP_CHECK(ev.create());
     int n = 0;
     for (int B : widths) {
-        if (B > R || B > widest || (dtype == FTLM_F64 && (B > 16 || B == 10 || B == 12))) continue;
-        // B chains of the sector (their state fits the workspace sized for
-        // R >= B); two Lanczos steps per repetition, the first one a warm-up
+        // B chains of the sector (their state fits the workspace sized for R >=
+        // B); two Lanczos steps per repetition, the first one a warm-up, or a
+        // whole run where that is one launch
         LanczosJob job;
-        single_job(job, s, g, B, 3, dtype, work_dev);
-        float best_ms = 1e30f;
+        single_job(job, s, g, B, tiny ? kTuneSteps : 3, dtype, work_dev);
+        double best_ms = 1e30;
         for (int rep = 0; rep < 3; ++rep) {
-            int rc = job_start(job, 0, 0, FTLM_PM1, st);
-            if (rc == FTLM_OK) rc = job_steps(job, st, false, 1);
+            int rc = job_start(job, 0, 0, tiny ? FTLM_GAUSS : FTLM_PM1, st);
+            if (rc == FTLM_OK && !tiny) rc = job_steps(job, st, false, 1);
             if (rc == FTLM_OK && hipEventRecord(ev.e0, st) != hipSuccess) rc = FTLM_E_DEVICE;
-            if (rc == FTLM_OK) rc = job_steps(job, st, false, 1);
+            if (rc == FTLM_OK) rc = job_steps(job, st, false, tiny ? -1 : 1);
             if (rc == FTLM_OK && hipEventRecord(ev.e1, st) != hipSuccess) rc = FTLM_E_DEVICE;
             if (rc == FTLM_OK && hipEventSynchronize(ev.e1) != hipSuccess) rc = FTLM_E_DEVICE;
             if (rc != FTLM_OK) return rc == FTLM_E_DEVICE ? fail(rc, "autotune: HIP error") : rc;
             float ms = 0.f;
             HIP_CHECK(hipEventElapsedTime(&ms, ev.e0, ev.e1));
-            if (rep > 0) best_ms = std::min(best_ms, ms);  // the first rep warms up
+            if (rep > 0) best_ms = std::min(best_ms, double(ms));  // the first rep warms up
+        }
+        if (tiny) {  // per step of the longest chain
+            std::vector<Chain> ch(static_cast<size_t>(B));
+            HIP_CHECK(hipMemcpy(ch.data(), job.secs[0].chains, size_t(B) * sizeof(Chain), hipMemcpyDeviceToHost));
+            int steps = 1;
+            for (const Chain& c : ch) steps = std::max(steps, int(c.steps));
+            best_ms /= steps;
         }
         out->widths[n] = B;
         out->ms[n] = best_ms;
         ++n;
     }
     // A batch of x chains runs as the column chunks ftlm_lanczos cuts for it;
-    // its step costs the measured steps of those widths.
+    // its step costs the measured steps of those widths. The chains of a tiny
+    // sector run side by side: x of them cost what the next measured number does.
     auto measured = [&](int w) {
         for (int i = 0; i < n; ++i)
-            if (out->widths[i] == w) return out->ms[i];
+            if (out->widths[i] == w || (tiny && out->widths[i] > w)) return out->ms[i];
         return 1e300;  // not reached: every chunk width is a candidate <= R
     };
     auto batch_ms = [&](int x) {
+        if (tiny) return measured(x);
         double t = 0.0;
         for (auto [col, w] : column_chunks(x, dtype, lanczos_width(s->two_s, s->n_sites, dtype), true))
             t += measured(w);
@@ -757,6 +780,8 @@ int ftlm_plan_tune(ftlm_plan* p, void* stream, ftlm_plan_tuning* out) {
     const int* caps = p->dtype == FTLM_F32 ? caps32 : caps64;
     const int ncap = p->dtype == FTLM_F32 ? 6 : 3;
     const auto previous = p->job.chunks;
+    // a run on tiny sectors is one launch for all steps, whatever the split
+    const bool tiny = by_tiny_chains(p->job.launch());
     std::vector<std::vector<std::pair<int, int>>> seen;
     ftlm_plan_tuning t{};
     double best = 1e300;
@@ -768,9 +793,9 @@ int ftlm_plan_tune(ftlm_plan* p, void* stream, ftlm_plan_tuning* out) {
         float best_ms = 1e30f;
         for (int rep = 0; rep < 2; ++rep) {
             int rc = job_start(p->job, 0, 0, FTLM_PM1, p->stream);
-            if (rc == FTLM_OK) rc = job_steps(p->job, p->stream, false, 1);
+            if (rc == FTLM_OK && !tiny) rc = job_steps(p->job, p->stream, false, 1);
             if (rc == FTLM_OK && hipEventRecord(ev.e0, p->stream) != hipSuccess) rc = FTLM_E_DEVICE;
-            if (rc == FTLM_OK) rc = job_steps(p->job, p->stream, false, 1);
+            if (rc == FTLM_OK) rc = job_steps(p->job, p->stream, false, tiny ? -1 : 1);
             if (rc == FTLM_OK && hipEventRecord(ev.e1, p->stream) != hipSuccess) rc = FTLM_E_DEVICE;
             if (rc == FTLM_OK && hipEventSynchronize(ev.e1) != hipSuccess) rc = FTLM_E_DEVICE;
             float ms = 0.f;
@@ -779,7 +804,7 @@ int ftlm_plan_tune(ftlm_plan* p, void* stream, ftlm_plan_tuning* out) {
                 p->job.chunks = previous;
                 return rc == FTLM_E_DEVICE ? fail(rc, "plan tuning: HIP error") : rc;
             }
-            best_ms = std::min(best_ms, ms);
+            best_ms = std::min(best_ms, tiny ? ms / float(p->job.max_steps) : ms);
         }
         const int n = t.n_candidates++;
         t.max_width[n] = caps[i];

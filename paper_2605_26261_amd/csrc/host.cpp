@@ -229,17 +229,18 @@ int job_start(LanczosJob& job, uint64_t seed, uint64_t r0, int dist, hipStream_t
 int job_steps(const LanczosJob& job, hipStream_t st, bool timed, int nsteps) {
     LanczosLaunch a = job.launch();
     const int n = nsteps < 0 ? job.max_steps : nsteps;
-    // a whole run on tiny sectors takes one launch a chunk, unless its H.x
-    // launches are to be timed one by one
+    // a whole run on tiny sectors takes one launch, unless its H.x launches are to
+    // be timed one by one
     if (nsteps < 0 && by_tiny_chains(a) && !(timed && HvTimer::wanted())) {
         int n_bonds = 0;
         for (const BondTable& b : job.bonds) n_bonds = std::max(n_bonds, b.n_bonds);
-        for (auto [col, width] : job.chunks) {
-            a.col0 = a.block0 = uint32_t(col);
-            a.block_ld = uint32_t(width);
-            a.vb = width;
-            HIP_CHECK(launch_tiny_chains(a, n_bonds, st));
-        }
+        ChainBlocks blocks{};
+        for (auto [col, width] : job.chunks)
+            for (int c = col; c < col + width; ++c) {
+                blocks.first[c] = uint8_t(col);
+                blocks.width[c] = uint8_t(width);
+            }
+        HIP_CHECK(launch_tiny_chains(a, blocks, n_bonds, st));
         return FTLM_OK;
     }
     for (int k = 1; k <= n; ++k) {

@@ -194,10 +194,14 @@ hipError_t launch_neighbors_spin(const SectorDev& s, const BondTable& B, uint64_
 hipError_t launch_hv_lanczos(const LanczosLaunch& a, size_t lds, hipStream_t st);
 hipError_t launch_start(const LanczosLaunch& a, hipStream_t st);
 hipError_t launch_update(const LanczosLaunch& a, hipStream_t st);
-// Every step of a launch whose sectors are all tiny, in one kernel (n_bonds: the
-// most bonds of a sector's graph).
+// Every step of all chains of a job whose sectors are all tiny, in one kernel: the
+// first column and the columns of the vector block that holds each chain
+// (block_of), and the most bonds of a sector's graph.
+struct ChainBlocks {
+    uint8_t first[kMaxChains], width[kMaxChains];
+};
 bool by_tiny_chains(const LanczosLaunch& a);
-hipError_t launch_tiny_chains(const LanczosLaunch& a, int n_bonds, hipStream_t st);
+hipError_t launch_tiny_chains(const LanczosLaunch& a, const ChainBlocks& blocks, int n_bonds, hipStream_t st);
 hipError_t launch_chain_init(const LanczosLaunch& a, hipStream_t st);
 
 // Sector table builders and index kernels (sector.hip).

@@ -398,14 +398,16 @@ inline size_t tiny_partner_lds(uint64_t dim, int n_bonds) {
 // are those of the step-by-step kernels: a wave's 64 rows by fold, a tile's four
 // waves in order, the tiles by the fold of the first wave.
 template <typename L, typename T>
-__global__ __launch_bounds__(kTinyThreads) void tiny_chain_kernel(LanczosLaunch a, int partners) {
+__global__ __launch_bounds__(kTinyThreads) void tiny_chain_kernel(LanczosLaunch a, ChainBlocks blocks, int partners) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ BondTable B;
     __shared__ double psum[4 * kTinyTiles];
     __shared__ Chain chain;
     __shared__ double tot;
     const SecWork& sw = a.secs[blockIdx.y];
-    const int col = int(a.col0 + blockIdx.x);
+    const int col = int(blockIdx.x);
+    a.block0 = blocks.first[col];
+    a.block_ld = blocks.width[col];
     const SectorDev S = uniform(sw.S);
     const uint32_t dim = S.dim, groups = 4u * ((dim + kBlock - 1) / kBlock);
     const int lane = threadIdx.x & 63;
@@ -547,7 +549,7 @@ hipError_t launch_chain_init(const LanczosLaunch& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_tiny_chains(const LanczosLaunch& a, int n_bonds, hipStream_t st) {
+hipError_t launch_tiny_chains(const LanczosLaunch& a, const ChainBlocks& blocks, int n_bonds, hipStream_t st) {
     size_t lds = tiny_chain_lds(a.max_dim, a.n_sites, a.dtype == 0 ? 4 : 8);
     const size_t rows = tiny_partner_lds(a.max_dim, n_bonds);
     const int partners = lds + rows <= kTinyLds ? 1 : 0;
@@ -558,7 +560,8 @@ hipError_t launch_tiny_chains(const LanczosLaunch& a, int n_bonds, hipStream_t s
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     int(lds));
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(unsigned(a.vb), unsigned(a.nsec)), dim3(kTinyThreads), lds, st, a, partners);
+        hipLaunchKernelGGL(kern, dim3(unsigned(a.ld), unsigned(a.nsec)), dim3(kTinyThreads), lds, st, a, blocks,
+                           partners);
         return hipGetLastError();
     };
     if (a.n_sites > 32) return a.dtype == 0 ? go(tiny_chain_kernel<uint64_t, float>) : go(tiny_chain_kernel<uint64_t, double>);

@@ -257,13 +257,15 @@ int ftlm_lanczos(const ftlm_sector* s, const ftlm_graph* g, uint64_t seed, uint6
 /* ftlm_lanczos_noalloc: for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc). It runs ftlm_lanczos, same kernels and same results bit for
- * bit, with the workspace taken from a device array of
- * FTLM_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on
- * until the process ends; it allocates no device memory. Arguments are those
- * of ftlm_lanczos without work_dev/work_bytes. The sector's tables must sit
- * on the current device (FTLM_E_INVALID otherwise). A call whose workspace
- * (ftlm_lanczos_workspace_bytes(s, R, dtype)) exceeds the array returns
- * FTLM_E_RANGE before any device work. Every call on a GPU shares that GPU's
+ * bit, with the workspace taken from a device array that the library holds on
+ * each GPU it runs on until the process ends; it allocates no device memory.
+ * Arguments are those of ftlm_lanczos without work_dev/work_bytes. The sector's
+ * tables must sit on the current device (FTLM_E_INVALID otherwise). A call whose
+ * workspace (ftlm_lanczos_workspace_bytes(s, R, dtype)) exceeds
+ * FTLM_NOALLOC_SCRATCH_BYTES returns FTLM_E_RANGE before any device work. FP32
+ * chains of a sector of more than 2^18 states take up to a thousandth more for
+ * their reductions than FP64 ones; that excess does not count, and the array holds
+ * 64 KiB besides for it. Every call on a GPU shares that GPU's
  * array, which keeps the last call's contents (each call clears the counters
  * and chain state it needs): calls that overlap on one GPU, from two streams
  * or two threads, race and must not be made. */

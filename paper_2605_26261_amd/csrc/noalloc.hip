@@ -16,8 +16,8 @@ namespace {
 
 constexpr size_t kScratchBytes = FTLM_NOALLOC_SCRATCH_BYTES;
 // The consecutive slots of FP32 chains (slot_rows) take up to a thousandth more
-// than strided ones would. The limit counts the latter, so that it is the same
-// chains that fit.
+// of a workspace than strided ones would. The limit counts the latter, so that it
+// is the same chains that fit.
 constexpr size_t kSlotBytes = size_t(64) << 10;
 constexpr int kMaxDevices = 64;
 
@@ -56,9 +56,9 @@ extern "C" int ftlm_lanczos_noalloc(const ftlm_sector* s, const ftlm_graph* g, u
     const size_t slots = align256(partial_bytes(s->dim, R, dtype)) - align256(partial_bytes(s->dim, R, FTLM_F64));
     if (need - slots > kScratchBytes || need > sizeof(scratch))
         return fail(FTLM_E_RANGE,
-                    "R = %d chains of a sector of dimension %llu need %zu bytes of workspace; the no-alloc scratch "
-                    "holds %zu",
-                    R, (unsigned long long)s->dim, need - slots, kScratchBytes);
+                    "R = %d chains of a sector of dimension %llu need %zu bytes of workspace, %zu of which count; the "
+                    "no-alloc scratch holds %zu of those",
+                    R, (unsigned long long)s->dim, need, need - slots, kScratchBytes);
     int dev = -1;
     void* work = nullptr;
     if (int rc = scratch_on_current_device(&dev, &work)) return rc;

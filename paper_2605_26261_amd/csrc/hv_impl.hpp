@@ -17,7 +17,7 @@ namespace ftlm {
 // turns +J_b/4 into -J_b/4).
 // A partner index is in [0, D) by construction; it is clamped there anyway so
 // that a defect in the index arithmetic shows up as a parity failure and
-// never as an access outside x.
+// never as an access outside x (by runs: at most a run's length past it, see kRunRows).
 template <typename T, int VB, int SG = 2, bool BUF = false>
 struct GatherVisitor {
     static_assert(!BUF || VB == 1, "buffer-resource gathers serve single vectors");

@@ -152,6 +152,12 @@ struct RunBonds {
 
 constexpr uint32_t kNoRow = 0x80000000u;  // a byte offset past every buffer: loads return 0 and touch nothing
 
+// Rows of a run at most (C(14, 7) = 3432; general spin 1107). A bond's buffer
+// begins at a row of x, where its partners' run begins, and ends after this many:
+// a defect in the ranks would read a run's length past x at most. (The rest of x
+// as each bond's end cost one column 2 to 5 %.)
+constexpr uint32_t kRunRows = 3432;
+
 // A buffer of `bytes` bytes at address hi:lo.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t run_rsrc(uint32_t lo, uint32_t hi, uint32_t bytes) {
     void* p = reinterpret_cast<void*>(uint64_t(lo) | (uint64_t(hi) << 32));
@@ -216,6 +222,7 @@ __device__ __forceinline__ void run_block(const SectorDev& S, const BondTable& B
     const unsigned char* xb = reinterpret_cast<const unsigned char*>(x + col0);
     const int n_bonds = __builtin_amdgcn_readfirstlane(B.n_bonds);
     const int n_high = __builtin_amdgcn_readfirstlane(int(B.ends[low_bits]));
+    const uint32_t bytes = uniform(kRunRows * ldb);
     const T jsum4 = sizeof(T) == 4 ? T(B.jsum4_f) : T(B.jsum4_d);
     const uint16_t* pat = kLow.pattern + kLow.first[run.k];
     // rows by their position in the run (p0 may lie before it)
@@ -260,7 +267,7 @@ __device__ __forceinline__ void run_block(const SectorDev& S, const BondTable& B
                 const int b = __builtin_ctzll(fl);
                 fl = (fl & (fl - 1)) | (uint64_t(1) << kSetBonds);
                 sl.c[g] = lane_val(rb.coef, b);
-                const auto rs = run_rsrc(lane_u32(rb.blo, b), lane_u32(rb.bhi, b), b < kSetBonds ? kNoRow : 0u);
+                const auto rs = run_rsrc(lane_u32(rb.blo, b), lane_u32(rb.bhi, b), b < kSetBonds ? bytes : 0u);
 #pragma unroll
                 for (int i = 0; i < R; ++i) buffer_row<T, VB>(rs, voff[i], sl.v[g][i]);
                 ah += sl.c[g];
@@ -274,7 +281,7 @@ __device__ __forceinline__ void run_block(const SectorDev& S, const BondTable& B
                 const uint32_t pm = lane_u32(rb.mask, bb);
                 const uint32_t mask = pm & 0x3fffffffu, odd = pm >> 30;
                 sl.c[g] = lane_val(rb.coef, bb);
-                const auto rs = run_rsrc(lane_u32(rb.blo, bb), lane_u32(rb.bhi, bb), kNoRow);
+                const auto rs = run_rsrc(lane_u32(rb.blo, bb), lane_u32(rb.bhi, bb), bytes);
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
                     const uint32_t no = (uint32_t(__popc(l2[i] & mask)) + odd) << 31;  // kNoRow unless the row flips

@@ -211,6 +211,7 @@ __device__ __forceinline__ void spin_run_block(const SectorDev& S, const BondTab
     const int lane = threadIdx.x & 63;
     const uint32_t ldb = uint32_t(ld * sizeof(T));
     const unsigned char* xb = reinterpret_cast<const unsigned char*>(x + col0);
+    const uint32_t bytes = uniform(kRunRows * ldb);
     const int n_bonds = uniform(B.n_bonds);
     const int n_high = uniform(int(B.ends[L.sites]));
     const uint32_t* strings = L.digits + uniform(*gptr(L.first + run.k));
@@ -264,7 +265,7 @@ __device__ __forceinline__ void spin_run_block(const SectorDev& S, const BondTab
                 const int t = __builtin_ctzll(fl);
                 fl = (fl & (fl - 1)) | (uint64_t(1) << kNoTerm);
                 const T w = lane_val(st.w, t);
-                const auto rs = run_rsrc(lane_u32(st.blo, t), lane_u32(st.bhi, t), t < kNoTerm ? kNoRow : 0u);
+                const auto rs = run_rsrc(lane_u32(st.blo, t), lane_u32(st.bhi, t), t < kNoTerm ? bytes : 0u);
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
                     sl.w[g][i] = w;
@@ -302,7 +303,7 @@ __device__ __forceinline__ void spin_run_block(const SectorDev& S, const BondTab
             }
         };
         auto fetch = [&](auto& sl, int g, int b, int e) {
-            const auto rs = run_rsrc(lane_u32(st.blo, 2 * b + e), lane_u32(st.bhi, 2 * b + e), kNoRow);
+            const auto rs = run_rsrc(lane_u32(st.blo, 2 * b + e), lane_u32(st.bhi, 2 * b + e), bytes);
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 sl.w[g][i] = w[e][i];

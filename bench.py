@@ -2,14 +2,14 @@
 
 Workload: the spin-1/2 Heisenberg icosidodecahedron (N = 30, 60 bonds, J = 1),
 S^z = 0 sector (D = C(30,15) = 155,117,520), R = 20 Gaussian start vectors
-(seed 2), M = 100 Lanczos steps, FP32 vectors with FP64 alpha/beta, run with
-both index maps (compressed lookup table and combinatorial ranking).
+(seed 2), M = 100 Lanczos steps, FP32 vectors with FP64 alpha/beta, run once with
+each index map and then W untimed and K timed times with the fastest.
 
 One step = one full FTLM pass over the batch: start vectors, M batched
 Lanczos steps (multi-vector H.x with fused alpha, update with fused beta),
 the host Ritz solves and the thermal reduction. Sector tables are built once
 before timing (inputs resident in HBM). The headline value is H.x
-states.bonds/s over the whole job (D * N_B per vector-H.x) for the faster
+states.bonds/s over the whole job (D * N_B per vector-H.x) with the fastest
 index map; the line also carries FTLM samples/s, the H.x kernel's roofline
 and the FP64 CPU oracle timed on a bounded sample of the same product.
 
@@ -87,6 +87,19 @@ def timed_hv(ftlm, torch, sec, g, x, y, reps):
     return times[len(times) // 2]
 
 
+def run_passes(modes, warmup, steps, measure):
+    """One pass with each index map, then `warmup` untimed and `steps` timed
+    ones with the fastest: the maps differ by less than a pass's spread at this
+    size, and one pass takes seconds. measure(mode, warmup, steps, first) returns
+    a map's record; the fastest map's is the one over `steps` passes, with the
+    tuning and the product sweep of its first."""
+    results = {m: measure(m, 0, 1, True) for m in modes}
+    best = max(results, key=lambda m: results[m]["states_bonds_per_s"])
+    once = {k: results[best][k] for k in ("autotune_ms", "hv_width_sweep")}
+    results[best] = {**measure(best, warmup, steps, False), **once}
+    return best, results
+
+
 def run_gpu(args):
     import numpy as np
     import torch
@@ -99,9 +112,9 @@ def run_gpu(args):
     g = ftlm.Graph(N_SITES, bonds)
     n_bonds = g.n_bonds
     temps = driver.log_temperatures()
-    results = {}
     all_modes = {"clt": ftlm.CLT, "cr": ftlm.CR, "full": ftlm.FULL, "lin": ftlm.LIN}
-    for mode_name in args.modes.split(","):
+
+    def measure(mode_name, warmup, steps, sweep_widths):
         mode = all_modes[mode_name]
         sec = ftlm.Sector(N_SITES, N_UP, mode, device=dev)
         dim = sec.dim
@@ -124,7 +137,7 @@ def run_gpu(args):
             th = ftlm.thermo(N_SITES, [rec], temps, 1.0)
             return rec, th
 
-        for _ in range(args.warmup):
+        for _ in range(warmup):
             step()
         torch.cuda.synchronize()
         ftlm.stats_reset()
@@ -132,7 +145,7 @@ def run_gpu(args):
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         hv_count = 0
-        for _ in range(args.steps):
+        for _ in range(steps):
             rec, th = step()
             hv_count += int(rec["steps"].sum())
         torch.cuda.synchronize()
@@ -140,7 +153,7 @@ def run_gpu(args):
         ftlm.stats_enable(False)
         launches, hv_ms = ftlm.stats_read()
         # every batch launches M = min(M, D) steps
-        job_alg = args.steps * M * sum(hv_alg_bytes(dim, b) for _, b in batches)
+        job_alg = steps * M * sum(hv_alg_bytes(dim, b) for _, b in batches)
         # the roofline's launch: the widest one that a batch of B chains takes
         # (a batch may take several; at `width` chains a step is one launch)
         for width in sorted((w for w in LAUNCH_WIDTHS_F32 if w <= B), reverse=True):
@@ -156,14 +169,15 @@ def run_gpu(args):
                 break
         avg_ms = msb / nb
         alg = hv_alg_bytes(dim, width)
-        results[mode_name] = {
+        result = {
+            "passes": steps,
             "batch": B,
             "launch_width": width,
             "autotune_ms": tuned,
             "seconds": dt,
-            "ms_per_step": 1e3 * dt / args.steps,
+            "ms_per_step": 1e3 * dt / steps,
             "states_bonds_per_s": dim * n_bonds * hv_count / dt,
-            "samples_per_s": R * args.steps / dt,
+            "samples_per_s": R * steps / dt,
             "hv_launches": launches,
             "hv_job_alg_gbs": job_alg / (hv_ms * 1e-3) / 1e9,
             "hv_avg_ms": avg_ms,
@@ -172,12 +186,12 @@ def run_gpu(args):
             "hv_alg_gbs": alg / (avg_ms * 1e-3) / 1e9,
             "E0": float(rec["theta"][rec["theta"] != 0].min()),
         }
-        log(mode_name, json.dumps(results[mode_name]))
+        log(mode_name, json.dumps(result))
         # plain H.x (ftlm_hv) at several block widths: median of 20 launches
         del work
         torch.cuda.empty_cache()
         sweep = {}
-        for nv in (1, 4, 8, 10, 12, 16, 20, 32):
+        for nv in sweep_widths:
             x = torch.randn((dim, nv) if nv > 1 else (dim,), dtype=torch.float32, device=dev)
             y = torch.empty_like(x)
             ms = timed_hv(ftlm, torch, sec, g, x, y, 20)
@@ -186,17 +200,20 @@ def run_gpu(args):
                               "alg_gbs": a / (ms * 1e-3) / 1e9}
             del x, y
             torch.cuda.empty_cache()
-        results[mode_name]["hv_width_sweep"] = sweep
+        result["hv_width_sweep"] = sweep
         log(mode_name, "hv sweep", json.dumps(sweep))
         del sec
         torch.cuda.empty_cache()
-    return results, n_bonds
+        return result
+
+    return run_passes(args.modes.split(","), args.warmup, args.steps,
+                      lambda name, w, k, first: measure(name, w, k, (1, 4, 8, 10, 12, 16, 20, 32) if first else ())), n_bonds
 
 
 def plan_vs_plain():
     """The batched all-sector workload (6x4 J1-J2 lattice, 13 sectors, R = 32
     +-1 chains per sector, M = 80): one hipGraph-captured plan (one launch per
-    kernel per step over all sectors, its column split chosen by
+    kernel, block of columns and step over all sectors, the blocks chosen by
     ftlm_plan_tune) against the plain form (one sector and one chain at a
     time, eager). FTLM samples/s each."""
     import numpy as np
@@ -717,8 +734,7 @@ def main():
         print(f"bench.py measures one GPU only; --gpus {args.gpus} is not supported (use --gpus 1)",
               file=sys.stderr)
         sys.exit(2)
-    results, n_bonds = run_gpu(args)
-    best = max(results, key=lambda k: results[k]["states_bonds_per_s"])
+    (best, results), n_bonds = run_gpu(args)
     r = results[best]
     dom = results[best]
     traffic = None

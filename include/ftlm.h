@@ -306,8 +306,8 @@ int ftlm_autotune(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype, v
 
 /* ---- batched all-sector plans ---------------------------------------------
  * A plan runs R Lanczos chains in each of several S^z sectors of one graph
- * (for example every sector M >= 0) with one launch per kernel per Lanczos
- * step covering all sectors: each sector owns a contiguous range of
+ * (for example every sector M >= 0) with one launch per kernel, block of columns
+ * and Lanczos step, each covering all sectors: each sector owns a contiguous range of
  * workgroups sized by its dimension (sectors of dimension 1 to 10^6+ in the
  * same launch), and the M-step loop can be captured once in a HIP graph and
  * replayed. Per-chain results are bitwise the same as ftlm_lanczos on the
@@ -369,10 +369,10 @@ void ftlm_plan_destroy(ftlm_plan* p);
  * one caller-owned arena. Requests are admitted in arrival order when their
  * HBM footprint fits the free arena (first fit) and fewer than max_active are
  * on the device; their tables, Krylov vectors and chain states stay on the
- * device until they finish. Each round advances every active request by one
- * Lanczos step, with one launch per kernel for all active requests of the
- * same N and R (sectors of different graphs and at different steps share
- * the launch). Finished requests leave at once and free their memory, so
+ * device until they finish. Each round advances every active request by
+ * steps_per_round Lanczos steps, with one launch per kernel, block of columns and
+ * step for all active requests of the same N and R (sectors of different graphs
+ * and at different steps share the launch). Finished requests leave at once and free their memory, so
  * waiting requests are admitted while others are still running. A request's
  * result does not depend on what else was on the device (each sector's
  * reduction order depends only on its dimension). */
@@ -384,7 +384,7 @@ typedef struct ftlm_server_opts {
     int32_t max_active;    /* requests on the device at once, 1..256 (0 = 16: a small active set
                               finishes the oldest requests first at the same throughput, since
                               every round still fills the device) */
-    int32_t batch_same_n;  /* 1: one launch per step for all active requests of equal N and R */
+    int32_t batch_same_n;  /* 1: the same launches for all active requests of equal N and R */
     int32_t steps_per_round;  /* Lanczos steps issued per round before finished requests are
                                  looked for, 1..64 (0 = 4); a request that finishes inside a
                                  round costs its remaining steps of the round one early return

@@ -1,7 +1,7 @@
 // Host-side machinery shared by the C ABI and the request server: error
 // reporting, sector/graph handles, start-vector keys, H.x timing hooks, column
-// chunking and the Lanczos job (one or many sectors, one launch per kernel
-// per step).
+// chunking and the Lanczos job (one or many sectors, one launch per kernel,
+// block of columns and step).
 #include "host.hpp"
 
 #include <cstdarg>

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kBlock) void hv_spin_runs_kernel(SectorDev S, BondT
     });
 }
 
-// The Lanczos step's H.x of a small sector (small_lanczos_items).
+// The Lanczos step's H.x of a small sector (small_lanczos).
 template <int MODE, typename T, int VB, int NT>
 __global__ __launch_bounds__(NT) void hv_spin_small_lanczos_kernel(LanczosLaunch a) {
     extern __shared__ __align__(16) unsigned char smem[];

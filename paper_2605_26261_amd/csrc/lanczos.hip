@@ -1,7 +1,9 @@
 // Lanczos kernels over a list of sectors: start vectors and the second half
 // of a Lanczos step (paper Sec. 2, the recursion after Eq. 3, without
 // reorthogonalization). The first half of a step (w = H q_k - beta_{k-1}
-// q_{k-1} and alpha_k) is hv_lanczos_kernel. A launch covers one sector or
+// q_{k-1} and alpha_k) is lanczos_rows_kernel (FP32, spin 1/2), hv_lanczos_kernel
+// or hv_spin_lanczos_kernel, for small sectors a kernel of lanczos_small.hpp;
+// tiny_chain_kernel takes both halves of all steps. A launch covers one sector or
 // every sector of a plan; each sector owns a contiguous range of blocks.
 #include <math.h>
 

@@ -390,8 +390,8 @@ def plan_workspace_bytes(graph, n_ups, mode, R, dtype):
 
 
 class Plan:
-    """ftlm_plan: R chains in each listed sector, one launch per kernel per
-    Lanczos step over all sectors; owns its device arena."""
+    """ftlm_plan: R chains in each listed sector, one launch per kernel, block of
+    columns and Lanczos step over all sectors; owns its device arena."""
 
     def __init__(self, graph, n_ups, mode, R, M, dtype, device="cuda", stream=None):
         self.n_ups = [int(v) for v in n_ups]

@@ -34,19 +34,15 @@ N_SITES, N_UP, R, M, SEED = 30, 15, 20, 100, 2
 LAUNCH_WIDTHS_F32 = (1, 2, 4, 8, 10, 12, 16, 20, 32)
 
 # Bytes between the L2 and the memory side per steady-state launch of the
-# dominant kernel (Lanczos-epilogue H.x over a block of FP32 columns, per
-# index map and block width), from rocprofv3 FETCH_SIZE and WRITE_SIZE runs
-# scaled by the counts of a 2 GiB copy and checked against request-size
-# counters (profiles/hv_lanczos_n30_r20_counters.md). The memory side
-# includes the Infinity Cache, so this bounds the HBM traffic from above.
-# They describe the kernel sources with this hash and are dropped otherwise.
+# dominant kernel (Lanczos-epilogue H.x over a block of FP32 columns, per block
+# width; every index map takes the same kernel at this size), from rocprofv3
+# FETCH_SIZE and WRITE_SIZE runs scaled by the counts of a 2 GiB copy
+# (profiles/hv_lanczos_n30_r20_counters.md). The memory side includes the Infinity
+# Cache, so this bounds the HBM traffic from above. They describe the kernel
+# sources with this hash and are dropped otherwise.
 KERNEL_SOURCES = ["layout.hpp", "device.hpp", "kernels.hpp", "rowloop.hpp", "rowio.hpp", "lowtab.hpp", "runs.hpp",
                   "hv_impl.hpp", "lanczos_rows.hpp", "hv_lanczos_f32.hip"]
-MEASURED_TRAFFIC = {"sources": "1123cd4f9861cbbe", "bytes": {
-    "clt": {1: 19.44e9, 2: 34.19e9, 4: 65.48e9, 8: 125.77e9, 10: 160.94e9, 12: 197.3e9, 16: 272.91e9, 20: 340.19e9},
-    "cr": {1: 13.41e9, 2: 26.88e9, 4: 55.84e9, 8: 112.51e9, 10: 153.01e9, 12: 190.25e9, 16: 250.94e9, 20: 338.26e9},
-    "full": {1: 99.57e9, 2: 111.91e9, 4: 147.91e9, 8: 210.6e9, 10: 253.37e9, 12: 286.72e9, 16: 367.8e9, 20: 433.01e9},
-    "lin": {1: 14.4e9, 2: 28.82e9, 4: 59.68e9, 8: 119.64e9, 10: 155.34e9, 12: 190.45e9, 16: 264.38e9, 20: 332.48e9}}}
+MEASURED_TRAFFIC = {"sources": "79edc43516e137cd", "bytes": {1: 17.23e9, 2: 32.75e9, 4: 56.65e9, 8: 119.58e9}}
 
 
 def kernel_source_hash():
@@ -670,12 +666,12 @@ def paper_cpu_method(target_s=10.0):
 
 
 def profile_kernels(batch=None):
-    """Short run for hardware-counter passes: per index map, a 3-step Lanczos
-    run over `batch` chains (when None, one at every FP32 launch width up to
-    R, so that whichever width the autotuner picks, the last two
-    Lanczos-epilogue H.x launches of its run are steady-state launches of the
-    FTLM pass) and 3 single-vector H.x launches; then an elementwise kernel
-    that reads 2 GiB and writes 2 GiB, to calibrate the byte counters."""
+    """Short run for hardware-counter passes, with combinatorial ranking: a
+    3-step Lanczos run over `batch` chains (when None, one at each width that the
+    launches of an FTLM pass take at this size, so that the last two
+    Lanczos-epilogue H.x launches of its run are steady-state ones) and 3 products
+    of 1, 2, 4 and 8 vectors; then an elementwise kernel that reads 2 GiB and
+    writes 2 GiB, to calibrate the byte counters."""
     import torch
 
     from ftlm_inputs import graphs
@@ -683,17 +679,17 @@ def profile_kernels(batch=None):
 
     dev = torch.device("cuda:0")
     g = ftlm.Graph(N_SITES, graphs.icosidodecahedron())
-    for mode in (ftlm.CLT, ftlm.CR, ftlm.FULL, ftlm.LIN):
-        sec = ftlm.Sector(N_SITES, N_UP, mode, device=dev)
-        for B in ([batch] if batch else [w for w in LAUNCH_WIDTHS_F32 if w <= R]):
-            log("profile: batch", B)
-            ftlm.lanczos(sec, g, SEED, 0, B, 3, ftlm.GAUSS, ftlm.F32)
-        x = torch.randn(sec.dim, dtype=torch.float32, device=dev)
+    sec = ftlm.Sector(N_SITES, N_UP, ftlm.CR, device=dev)
+    for B in [batch] if batch else [1, 2, 4, 8]:
+        log("profile: batch", B)
+        ftlm.lanczos(sec, g, SEED, 0, B, 3, ftlm.GAUSS, ftlm.F32)
+    for nv in (1, 2, 4, 8):
+        x = torch.randn((sec.dim, nv), dtype=torch.float32, device=dev)
         y = torch.empty_like(x)
         for _ in range(3):
             ftlm.hv(sec, g, x, y)
         torch.cuda.synchronize()
-        del sec, x, y
+        del x, y
         torch.cuda.empty_cache()
     # calibration: an elementwise kernel that reads 2 GiB and writes 2 GiB
     a = torch.empty(512 << 20, dtype=torch.float32, device=dev).fill_(1.0)
@@ -739,7 +735,7 @@ def main():
     dom = results[best]
     traffic = None
     if kernel_source_hash() == MEASURED_TRAFFIC["sources"]:
-        traffic = MEASURED_TRAFFIC["bytes"].get(best, {}).get(dom["launch_width"])
+        traffic = MEASURED_TRAFFIC["bytes"].get(dom["launch_width"])
     roof = {"bound": "hbm", "achieved": dom["hv_alg_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": dom["hv_alg_gbs"] / HBM_PEAK_GBS, "traffic": traffic,
             "traffic_unit": "bytes per launch between L2 and the memory side (2 x FETCH_SIZE + WRITE_SIZE, "

@@ -127,7 +127,10 @@ inline int max_launch_width(int two_s) { return two_s > 1 ? 8 : 32; }
 // 18 sites 55 / 76 / 111 us, 20 sites 133 / 130 / 163, 21 sites 236 / 208 / 239, 22
 // sites 394 / 357 / 365, 24 sites 1385 / 1212 / 1116, 26 sites 6321 / 5368 / 4973; 20
 // columns at 21 sites 119 in one launch, 148 as 16 and 4. 16 FP64 columns, 16 / 8:
-// 18 sites 65 / 78, 20 sites 177 / 148, 24 sites 1362 / 1156.
+// 18 sites 65 / 78, 20 sites 177 / 148, 24 sites 1362 / 1156. A sector of many
+// sites with few spins up is smaller than its sites say, and takes more launches
+// than one of its size would (24 sites, 21 up, 2,024 rows, 32 columns 100 us a step
+// in four launches).
 inline int lanczos_width(int two_s, int n_sites, int dtype) {
     if (two_s > 1) return max_launch_width(two_s);
     if (dtype != FTLM_F32) return n_sites <= 18 ? 16 : 8;

@@ -8,11 +8,11 @@ namespace ftlm {
 
 // Threads per workgroup of the kernels below: eight waves, or four
 // - at 32 columns, whose registers leave room for eight waves per CU: two
-//   workgroups take turns at their barriers (26-site cluster 5.75 -> 5.58 ms; 16
-//   columns were 6 % slower with four waves);
+//   workgroups take turns at their barriers (a step of 18 and 20 sites, half up, 55.0
+//   and 133 us, 57.0 and 137 with eight waves; 16 columns were 6 % slower with four);
 // - at 20 columns where less than a third of the spins are up, or down: twelve
-//   waves per CU hide more of the few partner loads (30 sites, 9 up: 3.90 -> 3.65
-//   ms; 24 sites, half up: 1.18 against 1.46);
+//   waves per CU hide more of the few partner loads (22 sites, 6 up: 54.2 and 55.0
+//   us; in a plan split that way, 30 sites, 9 up: 3.65 and 3.90 ms);
 // - above 34 sites row by row, where the Y values of eight waves would leave a
 //   CU one workgroup.
 // The sums over a launch keep the order of eight waves.

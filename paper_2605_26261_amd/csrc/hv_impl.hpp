@@ -282,6 +282,12 @@ constexpr int kRunGroup = 2;  // bonds a slot: 4 or 8 gave 3.3 and 4.1 ms for 4-
 // multiply-add, about 500 in all. From 16-byte rows on the lines missed in L2
 // bound it (that path gives 7 TB/s, whether the Infinity Cache holds the line
 // or not): four FP32 columns 9.4 -> 7.3 ms, eight 17.7 -> 14.4.
+//
+// Short runs lie together, in sectors with fewer up than down spins at the end,
+// and their waves take longest: a launch with a block for every tile begins with
+// them (25 sites, 11 up, two FP32 columns: 185 us in ascending order, 142 this way
+// and with 14 up; where a block takes several tiles, 29 sites, 10 up, one column:
+// 640 and 666).
 template <typename L, typename T, int VB>
 __global__ __launch_bounds__(kBlock) void hv_runs_kernel(SectorDev S, BondTable B, HvLaunch h) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -297,7 +303,8 @@ __global__ __launch_bounds__(kBlock) void hv_runs_kernel(SectorDev S, BondTable 
     const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
     const uint32_t block_rows = kWaves * h.chunk;
     const uint32_t ntiles = uint32_t((uint64_t(h.nrows) + block_rows - 1) / block_rows);
-    for_each_tile(ntiles, blockIdx.x, gridDim.x, h.super_shift, [&](uint32_t tile) {
+    for_each_tile(ntiles, blockIdx.x, gridDim.x, h.super_shift, [&](uint32_t i) {
+        const uint32_t tile = (ntiles & h.flip) + (i ^ h.flip);  // i, or ntiles - 1 - i
         const uint64_t r0 = uint64_t(tile) * block_rows + uint64_t(wave) * h.chunk;
         if (r0 >= h.nrows) return;
         const uint32_t n = h.nrows - uint32_t(r0) < h.chunk ? h.nrows - uint32_t(r0) : h.chunk;
@@ -645,6 +652,7 @@ hipError_t launch_hv_runs(const SectorDev& s, const BondTable& B, HvLaunch h, hi
     const uint64_t blocks = (uint64_t(h.nrows) + kWaves * h.chunk - 1) / (uint64_t(kWaves) * h.chunk);
     h.grid = int(blocks < 8 ? blocks : blocks < shape.blocks ? (blocks + 7) & ~uint64_t(7) : shape.blocks);
     h.super_shift = plain_super_shift(blocks, 6);
+    h.flip = 2 * s.n_up < s.n_sites && blocks <= shape.blocks ? ~0u : 0u;
     const size_t lds = (size_t(2) << h.low_bits) + size_t(s.n_sites) * size_t(s.bw) * 4;
     hipLaunchKernelGGL((hv_runs_kernel<L, T, VB>), dim3(unsigned(h.grid)), dim3(kBlock), lds, st, s, B, h);
     return hipGetLastError();

@@ -102,6 +102,7 @@ struct HvLaunch {
     int super_shift;
     int low_bits;    // run kernel: sites of a run's low part
     uint32_t chunk;  // run kernel: rows a wave takes at a time
+    uint32_t flip;   // run kernel: all ones where the last rows come first, else 0
 };
 
 // One sector of a Lanczos launch (one sector, all sectors of a plan, or the

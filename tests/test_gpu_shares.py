@@ -81,3 +81,14 @@ def test_small_shares_take_no_longer(large, small):
     share = us(*large)
     torch.cuda.empty_cache()
     assert share <= 2.2 * few, (share, few)
+
+
+# a sector and the one with its up and down spins exchanged have the same runs, in
+# reverse order: within 2 % in turn, 1.25 to 1.4 with the short runs last
+@pytest.mark.parametrize("n,few", [(25, 11), (27, 11)])
+def test_exchanged_spins_take_no_longer(n, few):
+    g = ftlm.Graph(n, graphs.j1j2_ring(n))
+    sectors = [ftlm.Sector(n, u, ftlm.CR) for u in (few, n - few)]
+    a, b = (call_us(sec, g, 2, sec.dim) for sec in sectors)
+    torch.cuda.empty_cache()
+    assert a <= 1.15 * b, (a, b)

@@ -92,3 +92,11 @@ def test_exchanged_spins_take_no_longer(n, few):
     a, b = (call_us(sec, g, 2, sec.dim) for sec in sectors)
     torch.cuda.empty_cache()
     assert a <= 1.15 * b, (a, b)
+
+
+# 64 columns take two launches of 32: twice the time of 32 columns within 2 %, 1.19
+# times that without a bound on the rows in flight
+def test_64_columns_take_no_longer_than_twice_32():
+    g, sec = ftlm.Graph(21, graphs.j1j2_ring(21)), ftlm.Sector(21, 8, ftlm.CR)
+    wide, half = (call_us(sec, g, cols, sec.dim) for cols in (64, 32))
+    assert wide <= 1.1 * 2 * half, (wide, half)

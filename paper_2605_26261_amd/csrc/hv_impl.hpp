@@ -430,13 +430,13 @@ __global__ __launch_bounds__(kBlock) void hv_lanczos_kernel(LanczosLaunch a) {
 // evicted before their reuse (N = 30, 20 columns: 40.5 -> 38.9 ms; two
 // workgroups 44.9). Narrower blocks keep the register-limited occupancy (8
 // columns: 15.9 against 18.1 ms with the floor, 16: 31.3 against 33.6).
-// A product of 32 columns over up to 2^18 rows has no such choice of rows in
-// flight (184,756 rows: 78.9 us without a floor, 82.2 with two workgroups, but 20
-// columns 44.9 and 42.9); 32 of 64 columns have (203,490 rows 221 us without, 184
-// with three; up to 184,756 rows equal). Rows of more than 32 columns that are not
-// whole lines take several launches, each of which fetches lines of its neighbours:
-// two workgroups (52 columns, 705,432 rows 666 us with three, 609 with two; 64
-// columns 526 and 565).
+// A product of 32 columns over few rows has no such choice of rows in flight: up to
+// 768 tiles all are resident at once, three to a CU, without a floor (722 tiles 78.9
+// us, 82.2 with two workgroups, but 20 columns 44.9 and 42.9); up to 1024 it would be
+// four (33 sites, 28 up, 928 tiles 126 us, 104 with two; 64 columns, 795 tiles 221
+// and 184). Rows of more than 32 columns that are not whole lines take several
+// launches, each of which fetches lines of its neighbours: two workgroups (52
+// columns, 705,432 rows 666 us with three, 609 with two; 64 columns 526 and 565).
 inline bool two_to_a_cu(const HvLaunch& h) {
     return h.dtype == 0 && h.vb >= 20 && h.ld % 32 != 0 && (h.ld > 32 || h.nrows <= (1u << 18));
 }
@@ -444,7 +444,8 @@ template <typename T, int VB>
 size_t hv_plain_lds_floor(const HvLaunch& h) {
     if (sizeof(T) != 4 || VB < 20) return 0;
     if (two_to_a_cu(h)) return size_t(72) * 1024;
-    return h.nrows <= (1u << 18) && h.ld <= 32 ? 0 : size_t(48) * 1024;
+    const uint64_t tiles = (uint64_t(h.nrows) + kBlock - 1) / kBlock;
+    return tiles <= 768 ? 0 : size_t(tiles <= 1024 ? 72 : 48) * 1024;
 }
 
 template <typename L, int MODE, typename T, int VB, bool BUF = false>

@@ -100,3 +100,11 @@ def test_64_columns_take_no_longer_than_twice_32():
     g, sec = ftlm.Graph(21, graphs.j1j2_ring(21)), ftlm.Sector(21, 8, ftlm.CR)
     wide, half = (call_us(sec, g, cols, sec.dim) for cols in (64, 32))
     assert wide <= 1.1 * 2 * half, (wide, half)
+
+
+# the exchanged sector again, 32 columns over 928 tiles: within 2 %, 1.2 times that
+# with four workgroups a CU
+def test_exchanged_spins_32_columns():
+    g = ftlm.Graph(33, graphs.j1j2_ring(33))
+    a, b = (call_us(sec, g, 32, sec.dim) for sec in (ftlm.Sector(33, 28, ftlm.CR), ftlm.Sector(33, 5, ftlm.CR)))
+    assert a <= 1.1 * b, (a, b)

@@ -570,6 +570,24 @@ hipError_t launch_hv_spin_runs(const SectorDev& s, const BondTable& B, HvLaunch 
     return hipGetLastError();
 }
 
+// Tiles from which on wide rows take one tile a block: 4096; ranked, with few terms,
+// rows of up to 32 bytes 16384 (s = 5/2, M = 16, 13,889 tiles, 8 FP32 columns 384 us
+// one tile a block, 331 on the persistent grid, but 418 and 517 with the table; s = 2,
+// M = 6, 37,313 tiles 802 and 934). A new block stages its tables while the others on
+// its CU work: with two, for the LDS they take, the persistent grid is the faster at
+// every size (s = 7/2, 12 sites, 15 down steps, 28,689 tiles, 8 and 16 FP32 columns
+// 709 and 2102 us, 1085 and 2708 one tile a block), with three for rows of up to 32
+// bytes that are no part of wider ones, to 2^18 tiles (s = 3, 19 down steps, 151,135
+// tiles 3.2 and 4.0 ms; s = 2, 433,423 tiles 13.3 and 11.7; 16 columns, two launches,
+// s = 7/2, 63,147 tiles 6.3 and 5.0).
+static uint32_t spin_few_tiles(const SectorDev& s, size_t row_bytes, bool whole, size_t lds) {
+    const size_t used = (lds + sizeof(BondTable) + 1279) / 1280 * 1280;  // LDS goes out in 1280 bytes
+    if (3 * used > 163840) return 1u << 30;
+    if (row_bytes > 32 || !whole) return 4096;
+    if (4 * used > 163840) return 1u << 18;
+    return s.mode == kModeCr && few_flips(s.n_up, s.n_sites * s.two_s) ? 16384 : 4096;
+}
+
 hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch& h0, hipStream_t st) {
     HvLaunch h = h0;
     const size_t row_bytes = size_t(h.vb) * (h.dtype == 0 ? 4 : 8);
@@ -577,13 +595,8 @@ hipError_t launch_hv_spin(const SectorDev& s, const BondTable& B, const HvLaunch
         if (h.dtype != 0) return launch_hv_spin_runs<double, 1>(s, B, h, st);
         return h.vb == 1 ? launch_hv_spin_runs<float, 1>(s, B, h, st) : launch_hv_spin_runs<float, 2>(s, B, h, st);
     }
-    // one tile a block from 4096 tiles on; ranked, with few terms, from 16384 (s = 5/2, M =
-    // 16, 13,889 tiles, 8 FP32 columns 384 us one tile a block, 331 on the persistent
-    // grid, but 418 and 517 with the table; s = 2, M = 6, 37,313 tiles 802 and 934)
-    const bool whole = h.ld == uint64_t(h.vb);
-    const bool few = s.mode == kModeCr && row_bytes <= 32 && whole && few_flips(s.n_up, s.n_sites * s.two_s);
-    walk_schedule(row_bytes, few ? 16384 : 4096, s.mode != kModeCr, h);
     const size_t lds = hv_spin_lds_bytes(s);
+    walk_schedule(row_bytes, spin_few_tiles(s, row_bytes, h.ld == uint64_t(h.vb), lds), s.mode != kModeCr, h);
     auto go = [&](auto tt, auto mm) {
         using T = decltype(tt);
         constexpr int MODE = decltype(mm)::value;

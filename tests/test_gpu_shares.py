@@ -108,3 +108,12 @@ def test_exchanged_spins_32_columns():
     g = ftlm.Graph(33, graphs.j1j2_ring(33))
     a, b = (call_us(sec, g, 32, sec.dim) for sec in (ftlm.Sector(33, 28, ftlm.CR), ftlm.Sector(33, 5, ftlm.CR)))
     assert a <= 1.1 * b, (a, b)
+
+
+# the exchanged sector at s = 7/2, whose tables take LDS for two workgroups a CU
+# only: 1.4 times the few-up sector's time, 2.1 with tables staged for every tile
+def test_large_tables_take_little_longer():
+    g = ftlm.Graph(12, graphs.icosahedron())
+    many, few = (call_us(sec, g, 8, sec.dim) for sec in (ftlm.Sector(12, a, ftlm.CR, two_s=7) for a in (69, 15)))
+    torch.cuda.empty_cache()
+    assert many <= 1.7 * few, (many, few)

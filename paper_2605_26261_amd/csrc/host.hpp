@@ -174,6 +174,7 @@ struct LanczosJob {
         a.items = items;
         for (const SecWork& w : secs) {
             a.max_dim = std::max<uint64_t>(a.max_dim, w.S.dim);
+            a.max_bw = std::max(a.max_bw, w.S.bw);
             a.xcd_items += int(xcd_items(w.items, 0));
             a.xcd_pairs += int(xcd_items((w.items + 1) / 2, 0));
         }

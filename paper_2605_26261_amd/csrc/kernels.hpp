@@ -139,6 +139,7 @@ struct LanczosLaunch {
     int grid;            // total blocks (sum of the sectors' G, 8-aligned)
     int items;           // work items of the persistent H.x (sum of the sectors' items)
     uint64_t max_dim;    // the largest sector dimension (host launch tuning)
+    int max_bw;          // the widest binomial table of a sector (LDS layout)
     uint64_t ld;         // columns of the run: row stride of the partials
     uint32_t col0;       // the launch's columns
     int vb;

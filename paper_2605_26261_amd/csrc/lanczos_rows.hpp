@@ -40,11 +40,12 @@ constexpr int run_item_log(int vb) { return vb == 1 ? 3 : vb == 2 ? 2 : vb <= 4 
 // 64-row groups of an item at most
 constexpr int item_groups(int path, int vb) { return 16 << (path == kPathRuns ? run_item_log(vb) : 0); }
 
-// LDS of the kernels: the binomial table (at most N (N + 3) entries), then a
-// [site][lane] slab of Y values per wave (ranking); by runs the rank table and
-// the binomial table. At least what the final sums need.
-inline size_t lanczos_rows_lds(int path, int n_sites, int low_bits, int threads) {
-    const size_t binom = (size_t(n_sites) * size_t(n_sites + 3) * 4 + 15) & ~size_t(15);
+// LDS of the kernels: the binomial table (the widest of the launch's sectors), then
+// a [site][lane] slab of Y values per wave (ranking); by runs the rank table and
+// the binomial table. At least what the final sums need. (64 sites, 5 up: with room
+// for any table, 17 KB, one workgroup a CU and 28.0 ms for eight columns, 16.2 with two.)
+inline size_t lanczos_rows_lds(int path, int n_sites, int max_bw, int low_bits, int threads) {
+    const size_t binom = (size_t(n_sites) * size_t(max_bw) * 4 + 15) & ~size_t(15);
     size_t n = 0;
     if (path == kPathRuns) n = (size_t(2) << low_bits) + binom;
     else if (path == kModeCr) n = binom + size_t(threads) * size_t(n_sites) * 4;
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
         for (int i = threadIdx.x; i < (1 << a.low_bits) / 2; i += NT) low[i] = *gptr(src + i);
         binom = low + (1 << a.low_bits) / 2;
     }
-    uint32_t* ylds = binom + ((a.n_sites * (a.n_sites + 3) + 3) & ~3) + wave * uint32_t(a.n_sites) * 64u + uint32_t(lane);
+    uint32_t* ylds = binom + ((a.n_sites * a.max_bw + 3) & ~3) + wave * uint32_t(a.n_sites) * 64u + uint32_t(lane);
     SectorDev S{};
     const T* x = nullptr;
     T* y = nullptr;
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(NT) void lanczos_rows_kernel(LanczosLaunch a) {
 template <typename L, int PATH, typename T, int VB, int NT = 512>
 hipError_t launch_lanczos_rows(LanczosLaunch a, hipStream_t st) {
     auto kern = lanczos_rows_kernel<L, PATH, T, VB, NT>;
-    size_t lds = lanczos_rows_lds(PATH, a.n_sites, a.low_bits, NT);
+    size_t lds = lanczos_rows_lds(PATH, a.n_sites, a.max_bw, a.low_bits, NT);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));

@@ -1,0 +1,29 @@
+"""GPU: Lanczos runs in sectors of many sites: their time, and the same bits at
+every number of chains."""
+import time
+
+import pytest
+import torch
+
+from ftlm_inputs import graphs
+from paper_2605_26261_amd import ftlm
+
+pytestmark = pytest.mark.gpu
+
+
+def run(n, n_up, R, M, dtype=ftlm.F32, best_of=1):
+    g, sec = ftlm.Graph(n, graphs.j1j2_ring(n)), ftlm.Sector(n, n_up, ftlm.CR)
+    work = torch.empty(ftlm.lanczos_workspace_bytes(sec, R, dtype), dtype=torch.uint8, device="cuda")
+    best = float("inf")
+    for _ in range(best_of):
+        t = time.perf_counter()
+        alpha, beta, steps = ftlm.lanczos(sec, g, 7, 0, R, M, ftlm.PM1, dtype, work=work)
+        best = min(best, time.perf_counter() - t)
+    return alpha, beta, steps, best / sec.dim
+
+
+# with room for any binomial table beside its Y values a workgroup of 62 sites would
+# not fit a CU's LDS twice: a row takes 1.1 times as long as one of 61 sites, 1.9 then
+def test_62_sites_take_little_longer_than_61():
+    t62, t61 = (run(n, 5, 8, 10, best_of=5)[3] for n in (62, 61))
+    assert t62 <= 1.4 * t61, (t62, t61)

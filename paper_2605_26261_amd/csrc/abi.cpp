@@ -466,12 +466,12 @@ struct TuneCache {
 // Steps of the timed runs of tiny sectors, at most.
 constexpr int kTuneSteps = 32;
 
-// "_c5": the candidate set, cost model and kernel set; a cache file written
+// "_c6": the candidate set, cost model and kernel set; a cache file written
 // under an older one is not reused.
 std::string tune_key(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype) {
     std::string k = "N" + std::to_string(s->n_sites) + "_s" + std::to_string(s->two_s) + "_u" +
                     std::to_string(s->n_up) + "_m" + std::to_string(s->mode) + "_t" + std::to_string(dtype) + "_R" +
-                    std::to_string(R) + "_c5_b";
+                    std::to_string(R) + "_c6_b";
     // the bond structure, so that two graphs with the same size do not share entries
     uint64_t h = 1469598103934665603ull;
     for (size_t b = 0; b < g->bi.size(); ++b) {
@@ -585,7 +585,7 @@ int ftlm_autotune(const ftlm_sector* s, const ftlm_graph* g, int R, int dtype, v
     auto batch_ms = [&](int x) {
         if (tiny) return measured(x);
         double t = 0.0;
-        for (auto [col, w] : column_chunks(x, dtype, lanczos_width(s->two_s, s->n_sites, dtype), true))
+        for (auto [col, w] : column_chunks(x, dtype, lanczos_width(s->two_s, s->n_sites, dtype, x), true))
             t += measured(w);
         return t;
     };

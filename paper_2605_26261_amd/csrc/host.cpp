@@ -190,7 +190,7 @@ void job_layout(LanczosJob& job, const std::vector<SectorDev>& devs, const std::
     job.grid = int(block);
     job.items = int(items);
     job.lds = lds;
-    job.chunks = job_chunks(job, lanczos_width(job.two_s, job.n_sites, dtype));
+    job.chunks = job_chunks(job, lanczos_width(job.two_s, job.n_sites, dtype, R));
 }
 
 // Start vectors of samples r0 .. r0 + R - 1 in every sector of the job.

@@ -130,10 +130,20 @@ inline int max_launch_width(int two_s) { return two_s > 1 ? 8 : 32; }
 // 18 sites 65 / 78, 20 sites 177 / 148, 24 sites 1362 / 1156. A sector of many
 // sites with few spins up is smaller than its sites say, and takes more launches
 // than one of its size would (24 sites, 21 up, 2,024 rows, 32 columns 100 us a step
-// in four launches).
-inline int lanczos_width(int two_s, int n_sites, int dtype) {
+// in four launches). From 36 sites on sectors within reach have few spins up, or down:
+// few partners to load, but many sites to rank. Up to 20 columns take one launch (20
+// in one / 8, 8 and 4: 36 sites, 7 down 2.61 / 3.01 ms, 10 up 99.8 / 95.1 with cluster
+// bonds, 90.8 / 92.5 on a ring, 40, 7 down 5.97 / 6.61, 52, 6 down 8.51 / 11.4; but 34,
+// 10 up 56.5 / 53.8, 33, 12 up 155 / 143); more of them 16 or 32 from 42 sites (32 in
+// one / 8 a launch: 40, 7 down 10.2 / 9.4, 42, 6 down 3.18 / 4.01, 52, 6 down 12.1 /
+// 15.7; 24 as 20 and 4 / 16 and 8 / 8 a launch: 44, 6 down 4.31 / 4.17 / 4.09 with
+// cluster bonds, 3.90 / 3.70 / 3.98 on a ring). FP64, 16 in one / 8 a launch: 47 sites,
+// 6 down 5.83 / 5.66 and 6.11 / 6.30, 52, 6 down 11.6 / 11.5 and 12.0 / 12.5.
+inline int lanczos_width(int two_s, int n_sites, int dtype, int R) {
     if (two_s > 1) return max_launch_width(two_s);
-    if (dtype != FTLM_F32) return n_sites <= 18 ? 16 : 8;
+    if (dtype != FTLM_F32) return n_sites <= 18 || n_sites >= 52 ? 16 : 8;
+    if (n_sites >= 36 && R <= 20) return 20;
+    if (n_sites >= 42) return R >= 32 ? 32 : 16;
     return n_sites <= 20 ? 32 : n_sites <= 22 ? 20 : 8;
 }
 int check_dtype(int dtype);

@@ -27,3 +27,20 @@ def run(n, n_up, R, M, dtype=ftlm.F32, best_of=1):
 def test_62_sites_take_little_longer_than_61():
     t62, t61 = (run(n, 5, 8, 10, best_of=5)[3] for n in (62, 61))
     assert t62 <= 1.4 * t61, (t62, t61)
+
+
+# 20 columns in one launch take twice as long as 8, three times as 8, 8 and 4
+def test_20_columns_take_little_longer_than_8():
+    t20, t8 = (run(47, 41, R, 8, best_of=4)[3] for R in (20, 8))
+    assert t20 <= 2.4 * t8, (t20, t8)
+
+
+# 376,992, 850,668 and 22,100 rows: whichever launches take a chain, it has the same bits
+@pytest.mark.parametrize("n,n_up", [(36, 31), (42, 5), (52, 3)])
+@pytest.mark.parametrize("dtype", [ftlm.F32, ftlm.F64])
+def test_same_bits(n, n_up, dtype):
+    most = run(n, n_up, 33, 6, dtype)
+    for R in (1, 8, 12, 16, 20, 23, 32):
+        some = run(n, n_up, R, 6, dtype)
+        for a, b in zip(some[:3], most[:3]):
+            assert (a == b[:R]).all(), R

@@ -568,10 +568,15 @@ inline double run_count(int n_sites, int n_up, int low_bits) {
 // wider, does: 1134 -> 991 in all), and 3 million lose (26 sites, 17 up: 156
 // -> 290 us); above 32 sites, where the row-by-row
 // kernel walks 64-bit labels, ten times as many still pay (34 sites, 10 up:
-// 10.7 -> 7.2 ms). 32-byte rows are bound by the lines they miss either way
+// 10.7 -> 7.2 ms; five with 16-byte rows). A Lanczos step of two or four FP32 columns,
+// whose row-by-row kernel keeps the rows in flight together, has `most8` and `most16`
+// = 6 and 2 (two: 34 sites, 10 up, 8.0 times as many, 9.1 ms row by row, 12.3 by runs,
+// 35, 11 up, 5.9 times 36.0 and 30.1; four: 34, 11 up, 4.9 times 24.0 and 30.3, 33,
+// 14 up, 1.25 times 68.1 and 65.6). 32-byte rows are bound by the lines they miss either way
 // and gain only in the largest sectors (N = 30: 15.9 -> 14.4 ms, N = 28 equal);
 // wider rows do not (16 FP32 columns: 31.2 against 32.2 ms).
-inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16, bool part = false) {
+inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16, bool part = false, double most8 = 10.0,
+                    double most16 = 5.0) {
     if (row_bytes > 32) return false;
     const RunShape shape = run_shape(row_bytes);
     if (s.n_sites <= shape.low_bits) return false;
@@ -583,7 +588,7 @@ inline bool by_runs(const SectorDev& s, size_t row_bytes, double least16, bool p
     const double runs = run_count(s.n_sites, s.n_up, shape.low_bits);
     if (runs <= unit) return true;
     if (row_bytes > 16) return false;
-    if (s.n_sites > 32 && dim >= 67108864.0) return runs <= (row_bytes <= 8 ? 10.0 : 5.0) * unit;
+    if (s.n_sites > 32 && dim >= 67108864.0) return runs <= (row_bytes <= 4 ? 10.0 : row_bytes <= 8 ? most8 : most16) * unit;
     return row_bytes <= 8 && dim >= 12582912.0 && runs <= (table && row_bytes <= 4 && !part ? 2.0 : 4.0) * unit;
 }
 

@@ -257,7 +257,7 @@ inline int lanczos_path(LanczosLaunch& a) {
     const size_t row_bytes = size_t(a.vb) * sizeof(float);
     a.low_bits = run_shape(row_bytes).low_bits;
     a.item_log = 0;
-    if (a.nsec == 1 && by_runs(s, row_bytes, 4.0)) {
+    if (a.nsec == 1 && by_runs(s, row_bytes, 4.0, false, 6.0, 2.0)) {
         const uint32_t slots = sector_items(s.dim, true);
         a.item_log = run_item_log(a.vb);
         const uint32_t least = 512u * uint32_t(run_lane_rows(a.vb));

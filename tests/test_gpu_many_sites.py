@@ -44,3 +44,10 @@ def test_same_bits(n, n_up, dtype):
         some = run(n, n_up, R, 6, dtype)
         for a, b in zip(some[:3], most[:3]):
             assert (a == b[:R]).all(), R
+
+
+# two columns take 1.05 times as long as one, 1.4 times by runs
+def test_few_columns_above_32_sites():
+    two, one = (run(34, 10, R, 6, best_of=3)[3] for R in (2, 1))
+    torch.cuda.empty_cache()
+    assert two <= 1.25 * one, (two, one)
